@@ -118,8 +118,11 @@ typedef struct {
   double fx, fy;        /* constant body force added to the model force     */
   double rho_ref;       /* FP32_SHIFTED: reference density of the storage
                            shift (<= 0: the smallest initial density)       */
-  /* Launch shape; 0 selects the tuned default (see lbm_autotune).  Results
-     do not depend on these, only the speed does. */
+  /* Launch shape; 0 selects the tuned default (see lbm_autotune).  With all
+     of tile_x, tile_y, kernel_flags and tile_rounds 0 (and A = 0), a lattice
+     too small to fill the device with strips runs on patches: rectangular
+     tiles that take several steps per launch in LDS (lbm_launch_info shows
+     which).  Results do not depend on these, only the speed does. */
   int32_t tile_x;       /* columns per workgroup strip: 0, 64 or 256         */
   int32_t tile_y;       /* rows per workgroup segment: 1 .. 1024, or 0: set at
                            the first step so that the tiles fill whole rounds
@@ -229,10 +232,12 @@ lbm_status lbm_destroy(lbm_ctx* ctx);
 /* The launch shape that carries a run (not part of the paper's method; it
  * lets a caller relate measured kernel times to the work of one launch). */
 typedef struct {
-  int32_t steps_per_launch; /* 2 where two steps run per launch, else 1     */
-  int32_t strip;            /* columns per workgroup strip of that kernel    */
-  int32_t segment;          /* rows per segment; 0 until the first lbm_step
-                               has fixed an automatic height                 */
+  int32_t steps_per_launch; /* 2 where two steps run per launch, up to 8 on
+                               patches, else 1                               */
+  int32_t strip;            /* columns per workgroup strip (or patch tile) of
+                               that kernel                                   */
+  int32_t segment;          /* rows per segment (or tile); 0 until the first
+                               lbm_step has fixed an automatic height        */
   int32_t workgroups;       /* workgroups per launch (0 before that step)    */
   int32_t threads;          /* threads per workgroup                         */
   int32_t reserved[3];
@@ -247,7 +252,8 @@ lbm_status lbm_launch_info(const lbm_ctx* ctx, lbm_launch* out);
  * height, store kind, register cap, pipelined row loop, one or two steps
  * per launch and the two-step kernel's strip width), `steps` steps each, on
  * a scratch state started from d_rho0, and return the fastest in
- * best->tile_x / tile_y / kernel_flags (the other fields are copied from p).
+ * best->tile_x / tile_y / kernel_flags (the other fields are copied from p;
+ * all three 0: the default shape, where that is patches).
  * Uses d_workspace (lbm_workspace_bytes(p)); synchronises the stream; the
  * results of a run never depend on the choice, only its speed. */
 lbm_status lbm_autotune(const lbm_params* p, void* d_workspace, size_t bytes,

@@ -28,6 +28,8 @@
 //      read from the 3x3 LDS stencil, and store it.
 // Halo rows at the segment ends and the H halo columns are recomputed from
 // the populations.  No MFMA: the update is a bandwidth-bound stencil.
+// Lattices too small to fill the device with strips run on patches instead
+// (patch_steps): several steps per launch of a rectangular tile held in LDS.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -1572,6 +1574,301 @@ __device__ __forceinline__ void tile_fe_pipe(const S* __restrict__ src, S* __res
   chk_commit<CHK>(ck, dmax, s_du);
 }
 
+// ---- patch steps: T time steps of one tile in LDS ------------------------------
+// A lattice too small to fill the device with strips runs on patches: a
+// workgroup takes a tile of tx x ty nodes through T steps in one launch, with
+// the populations between the steps in LDS and nothing exchanged between
+// workgroups.  A step reads H nodes around what it updates (H = 2 for the
+// pseudopotential: pull + psi stencil; 3 for the free energy: pull + the
+// chemical-potential and gradient stencils), so the workgroup holds the tile
+// plus H T - 1 nodes a side and the valid part shrinks by H a side per step;
+// neighbouring workgroups repeat those halo nodes.  Per step s = 1 .. T:
+//   A: pull (step 1 from memory, later ones from the LDS populations), the
+//      density (FE) or psi (P) into LDS;
+//   B: (FE) chemical potential into LDS;
+//   C: collide, populations to LDS (the last step: to memory).
+// Every thread keeps its NPT nodes throughout: their LDS addresses are formed
+// once, and one compare of a node's depth (H T - 1 at the tile, less by its
+// distance from the tile) says whether a phase of a step includes it.  A node's
+// pulled populations stay in registers from A to C, so the LDS populations
+// are updated in place: C writes after the barrier that ends A.  They lie
+// node by node, nine values each: an odd number of values, so neighbouring
+// lanes do not conflict, and one address serves a node's nine accesses.
+// A dimension that one tile spans has no halo (wrapx, wrapy): rows wrap in a
+// node's row addresses, and the two edge columns are written twice, the
+// second time into a ghost column on the other side.
+// What bounds it on a small lattice is the chain of instructions and barriers
+// of a step (about one wavefront per SIMD), and the launch with its memory
+// round trips, which T shares out.
+// Every node does the single-step kernels' arithmetic in the same order and
+// each step's output is rounded to the storage type, so T steps here equal T
+// single steps bit for bit.
+struct PatchShape {
+  int tx, ty;        // nodes of a tile (the last ones of a row or column clipped)
+  int ntx, nty;      // tiles along x and y
+  int steps;         // T
+  int wrapx, wrapy;  // 1: the tile spans the dimension (periodic inside LDS)
+  int xcd_remap;
+};
+
+// Halo nodes a side of a patch of T steps.
+__host__ __device__ constexpr int patch_halo(int model, int T) {
+  return (model == MODEL_P ? 2 : 3) * T - 1;
+}
+
+// LDS columns and rows of a patch (with ghost columns).
+__host__ __device__ inline int patch_pitch(int model, const PatchShape& ps) {
+  return ps.tx + 2 * (ps.wrapx ? 1 : patch_halo(model, ps.steps));
+}
+__host__ __device__ inline int patch_rows(int model, const PatchShape& ps) {
+  return ps.ty + (ps.wrapy ? 0 : 2 * patch_halo(model, ps.steps));
+}
+
+// Index i moved by at most n past either end of [0, n), wrapped.
+__device__ __forceinline__ int wrap1(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
+
+// 3x3 neighbourhood of an LDS plane: row starts of the rows below, at and
+// above the node, each at the node's own column.
+template <class C>
+__device__ __forceinline__ void gather_rows(const C* b, const C* m, const C* t, C v[9]) {
+  v[0] = m[0];
+  v[1] = m[1];
+  v[2] = t[0];
+  v[3] = m[-1];
+  v[4] = b[0];
+  v[5] = t[1];
+  v[6] = t[-1];
+  v[7] = b[-1];
+  v[8] = b[1];
+}
+
+// GEN = 1: walls, the collision drive and gravity, switched at run time as in
+// tile_p / tile_fe.
+template <int MODEL, int EOS, class S, class C, int NPT, int GEN>
+__device__ __forceinline__ void patch_steps(const S* __restrict__ src, S* __restrict__ dst,
+                                            const KParams<C>& kp, const PatchShape& ps,
+                                            unsigned* __restrict__ flags, int x0, int y0,
+                                            C* __restrict__ lds, unsigned* s_flag) {
+  constexpr int H = MODEL == MODEL_P ? 2 : 3;
+  const int nx = kp.nx, ny = kp.ny, T = ps.steps;
+  const int w = min(ps.tx, nx - x0), h = min(ps.ty, ny - y0);
+  const bool walls = GEN != 0 && kp.walls != 0;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const int halo = H * T - 1;
+  const int pitch = patch_pitch(MODEL, ps), cells = pitch * patch_rows(MODEL, ps);
+  C* const F = lds;              // populations, nine per node
+  C* const Aq = F + 9 * cells;   // density deviation (FE) or psi (P)
+  C* const Mu = Aq + cells + (GEN != 0 ? pitch : 0);  // FE: chemical potential (with
+                                                      // walls one row more each side)
+  // what the workgroup holds: columns xa .. xa+wa-1, rows ya .. ya+ha-1
+  const int xa = x0 - (ps.wrapx ? 0 : halo), wa = w + (ps.wrapx ? 0 : 2 * halo);
+  int ya = y0 - (ps.wrapy ? 0 : halo), yb = y0 + h + (ps.wrapy ? 0 : halo);
+  if (walls) {
+    ya = max(ya, 0);
+    yb = min(yb, ny);
+  }
+  const int ha = yb - ya, col0 = ps.wrapx ? 1 : 0;
+  const bool wall_lo = walls && ya == 0, wall_hi = walls && yb == ny;
+
+  int X[NPT], Y[NPT], dep[NPT];     // lattice position (unwrapped) and depth
+  int rm[NPT], r0[NPT], rp[NPT];    // LDS cells below, at and above the node
+  int ghost[NPT];                   // offset of the ghost cell it also writes, or 0
+  const float ia = __builtin_amdgcn_rcpf((float)wa);
+#pragma unroll
+  for (int q = 0; q < NPT; ++q) {
+    const int n = tid + q * nt;
+    // n / wa: the quotient's distance from an integer is at least 1 / (2 wa),
+    // far above the rounding for these sizes
+    const int iy = (int)(((float)n + 0.5f) * ia), ix = n - iy * wa;
+    X[q] = xa + ix;
+    Y[q] = ya + iy;
+    const int out = max(max(x0 - X[q], X[q] - (x0 + w - 1)), max(y0 - Y[q], Y[q] - (y0 + h - 1)));
+    dep[q] = n < wa * ha ? halo - max(out, 0) : -1;
+    int im = iy - 1, ip = iy + 1;
+    if (ps.wrapy) {
+      im = wrap1(im, ha);
+      ip = wrap1(ip, ha);
+    }
+    if (walls) {  // rows past a wall mirror the rows inside
+      if (Y[q] == 0) im = iy + 1;
+      if (Y[q] == ny - 1) ip = iy - 1;
+    }
+    const int c = col0 + ix;
+    rm[q] = im * pitch + c;
+    r0[q] = iy * pitch + c;
+    rp[q] = ip * pitch + c;
+    ghost[q] = ps.wrapx && ix == 0 ? wa : 0;
+    if (ps.wrapx && ix == wa - 1 && wa > 1) ghost[q] = -wa;
+  }
+  const bool one_col = ps.wrapx && wa == 1;  // a single column is both neighbours
+
+  // step 1 pulls from memory
+  C g[NPT][9];
+#pragma unroll
+  for (int q = 0; q < NPT; ++q) {
+    if (dep[q] < 0) continue;
+    const int xw = wrap1(X[q], nx), yw = wrap1(Y[q], ny);
+    pull9<S, C>(src, wrap1(yw - 1, ny) * kp.rowpitch, yw * kp.rowpitch,
+                wrap1(yw + 1, ny) * kp.rowpitch, colo(wrap1(xw - 1, nx)), colo(xw),
+                colo(wrap1(xw + 1, nx)), g[q]);
+  }
+
+  unsigned fl = 0;
+#pragma clang loop unroll(disable)
+  for (int s = 1; s <= T; ++s) {
+    const int da = H * (s - 1);  // depths of phases A, B (da + 1), C (da + H - 1)
+    if constexpr (NPT > 1 && sizeof(C) == 8) {
+      // form the byte addresses of the planes anew each step: hoisted out of
+      // the loop they take the registers that the collision needs (spills)
+#pragma unroll
+      for (int q = 0; q < NPT; ++q) asm volatile("" : "+v"(rm[q]), "+v"(r0[q]), "+v"(rp[q]));
+    }
+    C dr[NPT];
+    // ---- A
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      dr[q] = C(0);
+      if (dep[q] >= da) {
+        if (s > 1) {
+          const C* m = F + 9 * rm[q];
+          const C* z = F + 9 * r0[q];
+          const C* p = F + 9 * rp[q];
+          g[q][0] = z[0];
+          g[q][1] = z[-9 + 1];
+          g[q][2] = m[2];
+          g[q][3] = z[9 + 3];
+          g[q][4] = p[4];
+          g[q][5] = m[-9 + 5];
+          g[q][6] = m[9 + 6];
+          g[q][7] = p[9 + 7];
+          g[q][8] = p[-9 + 8];
+        }
+        if constexpr (GEN != 0) {
+          const int sd = walls ? wall_side(Y[q], ny) : 0;
+          if (sd) {
+            if constexpr (MODEL == MODEL_P) wall_fill(g[q], sd, kp.fy);
+            else wall_fill_fe(g[q], sd, kp);
+          }
+        }
+        dr[q] = sum9(g[q]);
+        const C rho = kp.rho_ref + dr[q];
+        fl |= domain_flags<MODEL, EOS>(rho, kp);
+        C a;
+        if constexpr (MODEL == MODEL_P) a = psi_of<EOS>(rho, kp, fl);
+        else a = dr[q];
+        Aq[r0[q]] = a;
+        if (ghost[q]) Aq[r0[q] + ghost[q]] = a;
+        if (one_col) Aq[r0[q] - 1] = a;
+      }
+    }
+    __syncthreads();
+    // ---- B
+    if constexpr (MODEL == MODEL_FE) {
+      auto mu_of = [&](const C v[9]) { return mu_dev<EOS>(v[0], kp) - kp.kappa * lap9(v); };
+#pragma unroll
+      for (int q = 0; q < NPT; ++q) {
+        if (dep[q] >= da + 1) {
+          C v[9];
+          gather_rows(Aq + rm[q], Aq + r0[q], Aq + rp[q], v);
+          const C mu = mu_of(v);
+          Mu[r0[q]] = mu;
+          if (ghost[q]) Mu[r0[q] + ghost[q]] = mu;
+          if (one_col) Mu[r0[q] - 1] = mu;
+        }
+      }
+      if (GEN != 0 && (wall_lo || wall_hi)) {
+        // the rows just past the walls, from the mirrored densities (in the
+        // mirrored order: the two sides of the mirror round differently)
+        for (int c = tid; c < 2 * wa; c += nt) {
+          const bool hi = c >= wa;
+          const int ix = hi ? c - wa : c;
+          if (hi ? !wall_hi : !wall_lo) continue;
+          if (!ps.wrapx && min(ix, wa - 1 - ix) < 1) continue;  // no column beside it
+          const C* e = Aq + (hi ? (ha - 1) * pitch : 0) + col0 + ix;  // the wall row
+          const int in = hi ? -pitch : pitch;                         // inward
+          C v[9];
+          if (hi) gather_rows(e, e + in, e + 2 * in, v);
+          else gather_rows(e + 2 * in, e + in, e, v);
+          const C mu = mu_of(v);
+          C* o = Mu + (hi ? ha * pitch : -pitch) + col0 + ix;
+          *o = mu;
+          if (ps.wrapx && ix == 0) o[wa] = mu;
+          if (ps.wrapx && ix == wa - 1) o[-wa] = mu;  // (a single column: both)
+        }
+      }
+      __syncthreads();
+    }
+    // ---- C
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      if (dep[q] < da + H - 1) continue;
+      C v[9];
+      gather_rows(Aq + rm[q], Aq + r0[q], Aq + rp[q], v);
+      const C rho = kp.rho_ref + dr[q];
+      C ux, uy;
+      const int sd = GEN != 0 && walls ? wall_side(Y[q], ny) : 0;
+      if constexpr (MODEL == MODEL_P) {
+        C sx, sy;
+        grad_sum(v, sx, sy);
+        C Fx = v[0] * sx + kp.fx;
+        C Fy = v[0] * sy + kp.fy;
+        C K = sx * sx + sy * sy;
+        C qs, qd, qxy;
+        q_terms(v, kp.qa, kp.qb, qs, qd, qxy);
+        if constexpr (GEN != 0) {
+          if (kp.ax != C(0)) Fx += drive_fx(kp, wrap1(X[q], nx), rho);
+          if (sd) wall_fx(g[q], sd, Fx);
+        }
+        collide<MODEL_P>(g[q], dr[q], rho, Fx, Fy, K, qs, qd, qxy, kp, ux, uy);
+      } else {
+        C m[9];
+        if (GEN != 0 && walls) gather_rows(Mu + (r0[q] - pitch), Mu + r0[q], Mu + (r0[q] + pitch), m);
+        else gather_rows(Mu + rm[q], Mu + r0[q], Mu + rp[q], m);
+        C grx, gry, gmx, gmy;
+        grad_sum(v, grx, gry);
+        grad_sum(m, gmx, gmy);
+        C Fx = -rho * gmx + kp.fx;
+        C Fy = -rho * gmy + kp.fy;
+        if constexpr (GEN != 0) {
+          if (kp.ax != C(0)) Fx += drive_fx(kp, wrap1(X[q], nx), rho);
+          if (sd) {
+            Fy = kp.fy;
+            gry = C(0);
+          }
+          if (kp.g != C(0)) Fy -= (rho - kp.grho0) * kp.g;
+          if (sd) wall_fx(g[q], sd, Fx);
+          const C pg = kp.grho0 * kp.g * (C(Y[q]) - kp.gy0);
+          const C dpg = kp.grho0 * kp.g;
+          collide<MODEL_FE>(g[q], dr[q], rho, Fx, Fy, grx, gry, C(0), C(0), kp, ux, uy, C(0), C(0),
+                            C(0), pg, dpg);
+        } else {
+          collide<MODEL_FE>(g[q], dr[q], rho, Fx, Fy, grx, gry, C(0), C(0), kp, ux, uy);
+        }
+      }
+      if (s == T) {
+        const int o = Y[q] * kp.rowpitch + colo(X[q]);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) dst[o + 64 * i] = (S)g[q][i];
+      } else {
+        C* f = F + 9 * r0[q];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) f[i] = (C)(S)g[q][i];
+        if (ghost[q]) {
+          C* f2 = f + 9 * ghost[q];
+#pragma unroll
+          for (int i = 0; i < 9; ++i) f2[i] = (C)(S)g[q][i];
+        }
+        if (one_col) {
+#pragma unroll
+          for (int i = 0; i < 9; ++i) f[i - 9] = (C)(S)g[q][i];
+        }
+      }
+    }
+    if (s < T) __syncthreads();
+  }
+  commit_flags(fl, flags, s_flag);
+}
+
 // ---- single-lattice step kernels --------------------------------------------
 template <int EOS, class S, class C, int BX, int NT, int WPE, int GEN = 0>
 __global__ __launch_bounds__(BX) __attribute__((amdgpu_waves_per_eu(WPE > 0 ? WPE : 1)))
@@ -1633,6 +1930,20 @@ void k_step_fe_pipe(const S* __restrict__ src, S* __restrict__ dst, const KParam
   tile_fe_pipe<EOS, S, C, BX, NT, 0>(src, dst, kp, flags, (tile % kp.nstrips) * BX,
                                      (tile / kp.nstrips) * kp.LY,
                                      ChkOut<C>{nullptr, nullptr, nullptr});
+}
+
+// Patch kernel: one workgroup per tile (patch_steps).  At most 1024 threads
+// of 128 registers: a whole CU's FP64 budget, or two workgroups in FP32.
+template <int MODEL, int EOS, class S, class C, int NPT, int GEN>
+__global__ __launch_bounds__(1024) void k_patch(const S* __restrict__ src, S* __restrict__ dst,
+                                                const KParams<C> kp, const PatchShape ps,
+                                                unsigned* __restrict__ flags) {
+  extern __shared__ __attribute__((aligned(16))) char patch_lds[];
+  __shared__ unsigned s_flag;
+  if (threadIdx.x == 0) s_flag = 0u;
+  const int tile = tile_index(ps.xcd_remap);
+  patch_steps<MODEL, EOS, S, C, NPT, GEN>(src, dst, kp, ps, flags, (tile % ps.ntx) * ps.tx,
+                                         (tile / ps.ntx) * ps.ty, (C*)patch_lds, &s_flag);
 }
 
 // Occupancy targets (waves per SIMD) of the register-capped variants.
@@ -2188,6 +2499,13 @@ struct LaunchCfg {
   int auto_ly;  // 1: segment height set at the first launch from occupancy
 };
 
+// Patch launches of a small lattice (patch_steps): off where strips serve it.
+struct PatchPlan {
+  bool on;
+  PatchShape ps;   // ps.steps: steps of a full launch
+  int threads, npt;  // threads per workgroup, nodes of a step per thread
+};
+
 }  // namespace
 
 struct lbm_ctx {
@@ -2201,6 +2519,7 @@ struct lbm_ctx {
   double rho_ref;  // storage shift reference (0 for FP64)
   double rho_ave;  // mean initial density (collision drive)
   LaunchCfg lc;
+  PatchPlan pp;
   int nstrips, nseg, xcd_remap;
   int nstrips2, nseg2, xcd_remap2;  // tiling of the two-step kernel (bx2 strips)
   KParams<double> kd;
@@ -2314,6 +2633,128 @@ void apply_launch(lbm_ctx* c) {
 // workgroups with no partly filled tail round; segments stay at least 16
 // rows so the halo rows remain a small overhead.
 bool two_step_ok(const lbm_ctx* c);
+bool needs_gen(const lbm_params& p);
+
+// Values of the compute type a patch keeps in LDS: nine populations and psi
+// or the density per cell, and the free energy's chemical potential (with
+// walls one row more each side).
+size_t patch_lds_values(const lbm_params& p, const PatchShape& ps) {
+  const size_t pitch = patch_pitch(p.model, ps), cells = pitch * patch_rows(p.model, ps);
+  return p.model == LBM_MODEL_FE ? 11 * cells + (needs_gen(p) ? 2 * pitch : 0) : 10 * cells;
+}
+
+// Compute units of the current device (256 on MI355X).
+int device_cus() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      cus < 1) {
+    (void)hipGetLastError();
+    return 256;
+  }
+  return cus;
+}
+
+// Costs in microseconds, fitted to MI355X timings of 3089 shapes (64^2 ..
+// 1448^2 lattices, tiles of 8 x 4 .. 64 x 16, 1 .. 8 steps per launch; rms
+// deviation 14 %): a launch costs l0; a round of resident workgroups costs lm
+// plus ld per wavefront of held nodes (the pulls and stores); a step costs
+// at least ls (its chain of instructions and barriers) or 0.4 ls plus kw per
+// wavefront that works on the compute unit.  strip_floor and strip_rate
+// (us per step, ns per node and step) are the strip kernels' own: their
+// latency on a small lattice and their rate on a large one, reached from
+// about 12 us above it; GEN rows are the general kernel's.
+struct PatchCost {
+  double l0, lm, ls, kw, ld, strip_floor, strip_rate;
+  int waves1, waves2;  // wavefronts a CU holds of the NPT = 1 and 2 kernels
+};
+const PatchCost& patch_cost(const lbm_params& p) {
+  static const PatchCost t[2][2][2] = {
+      // [model][FP32][GEN]
+      {{{1.4, 0.41, 1.56, 0.125, 0.176, 25, 0.0212, 24, 16},
+        {2.3, 0.00, 1.65, 0.151, 0.129, 25, 0.0294, 20, 16}},
+       {{2.6, 0.15, 1.25, 0.087, 0.079, 20, 0.0092, 32, 24},
+        {2.6, 0.15, 1.30, 0.100, 0.079, 20, 0.0145, 28, 20}}},
+      {{{1.9, 0.04, 1.56, 0.170, 0.187, 30, 0.0232, 16, 16},
+        {3.1, 0.00, 1.78, 0.300, 0.076, 33, 0.0300, 16, 16}},
+       {{1.9, 0.89, 1.53, 0.120, 0.055, 25, 0.0106, 32, 20},
+        {1.9, 0.89, 1.70, 0.150, 0.055, 25, 0.0155, 24, 16}}}};
+  return t[p.model == LBM_MODEL_P ? 0 : 1][p.precision == LBM_FP64 ? 0 : 1][needs_gen(p) ? 1 : 0];
+}
+
+// Patch launches for a lattice without an explicit launch shape, where their
+// estimated time per step is below the strips': tile, steps per launch and
+// threads of the least estimate.  In practice about one tile per compute
+// unit and 2 - 6 steps while the lattice has up to about 1000 nodes per
+// compute unit, and several tiles of up to 32 x 32 with 2 - 3 steps beyond.
+// Against the strips (which a lattice of few rows or columns leaves mostly
+// idle): 256 x 4 P FP64 10.4 -> 1.3 us per step, 256^2 P FP32 20.1 -> 2.2, FE
+// FP64 30.0 -> 3.6, 512^2 P FP64 25.5 -> 5.9, 1024^2 FE FP32 27.5 -> 17.8;
+// even at about 3 M nodes (P) and 1.5 M nodes (FE).
+PatchPlan plan_patch(const lbm_params& p) {
+  PatchPlan best{};
+  if (p.kernel_flags || p.tile_x || p.tile_y || p.tile_rounds || p.A != 0.0) return best;
+  const double N = (double)p.nx * p.ny;
+  const PatchCost& pc = patch_cost(p);
+  const bool gen = needs_gen(p), walls = p.boundary == LBM_BOUNDARY_WALLS;
+  const bool fp64 = p.precision == LBM_FP64, fe = p.model == LBM_MODEL_FE;
+  const int H = fe ? 3 : 2;
+  double best_us = std::max(pc.strip_floor, 12.0 + 1e-3 * pc.strip_rate * N);
+  if (N > 4e6 && !gen) return best;
+  static const int sides[] = {4, 8, 12, 16, 20, 24, 32, 48, 64};
+  const double cus = device_cus();
+  for (int sx : sides)
+    for (int sy : sides) {
+      if (sy > 32) continue;
+      for (int T = 1; T <= 8; ++T) {
+        PatchShape ps{};
+        const int halo = patch_halo(p.model, T);
+        ps.ntx = (p.nx + sx - 1) / sx;
+        ps.nty = (p.ny + sy - 1) / sy;
+        ps.tx = (p.nx + ps.ntx - 1) / ps.ntx;
+        ps.ty = (p.ny + ps.nty - 1) / ps.nty;
+        ps.steps = T;
+        // a patch that would reach around the lattice spans the dimension
+        if (ps.tx + 2 * halo + 2 > p.nx) {
+          ps.tx = p.nx;
+          ps.wrapx = 1;
+        }
+        if (!walls && ps.ty + 2 * halo + 2 > p.ny) {
+          ps.ty = p.ny;
+          ps.wrapy = 1;
+        }
+        ps.ntx = (p.nx + ps.tx - 1) / ps.tx;
+        ps.nty = (p.ny + ps.ty - 1) / ps.ty;
+        const int64_t cells = (int64_t)patch_pitch(p.model, ps) * patch_rows(p.model, ps);
+        const int npt = cells <= 1024 ? 1 : 2;
+        if (cells > 2048 || (npt == 2 && fe && gen && fp64)) break;  // larger T: more cells
+        const int64_t lds = (int64_t)patch_lds_values(p, ps) * (fp64 ? 8 : 4) + 64;
+        if (lds > 160 * 1024) break;
+        const int threads = (int)((cells + npt - 1) / npt + 63) / 64 * 64;
+        const double tiles = (double)ps.ntx * ps.nty;
+        const int occ = std::max(1, std::min((int)(160 * 1024 / lds),
+                                             (npt == 1 ? pc.waves1 : pc.waves2) / (threads / 64)));
+        const double conc = std::min((double)occ, std::ceil(tiles / cus));
+        const double rounds = std::max(1.0, std::ceil(tiles / (cus * occ)));
+        double t = pc.lm + pc.ld * cells / 64.0 * conc;
+        for (int s = 1; s <= T; ++s) {
+          // nodes of the step's first and last phase
+          const int e = H * (T - s), mx = ps.wrapx ? 0 : 2, my = ps.wrapy ? 0 : 2;
+          const double a = (double)(ps.tx + mx * (e + H - 1)) * (ps.ty + my * (e + H - 1));
+          const double c = (double)(ps.tx + mx * e) * (ps.ty + my * e);
+          t += std::max(pc.ls, 0.4 * pc.ls + pc.kw * 0.5 * (a + c) / 64.0 * conc);
+        }
+        const double us = (pc.l0 + rounds * t) / T;
+        if (us < best_us) {
+          best_us = us;
+          const int nt = ps.ntx * ps.nty;
+          ps.xcd_remap = (nt >= 16 && nt % 8 == 0) ? 1 : 0;
+          best = PatchPlan{true, ps, threads, npt};
+        }
+      }
+    }
+  return best;
+}
 
 template <class K>
 void tune_ly(lbm_ctx* c, K kernel, int bx, int nstrips) {
@@ -2502,6 +2943,50 @@ void launch_step2(lbm_ctx* c, const KParams<C>& kp) {
 
 bool two_step_ok(const lbm_ctx* c) {
   return c->lc.two && !needs_gen(c->p) && c->lc.bx == 256;
+}
+
+// One patch launch of m <= pp.ps.steps steps.
+template <int MODEL, int EOS, class S, class C, int NPT>
+void launch_patch(lbm_ctx* c, const KParams<C>& kp, int m) {
+  PatchShape ps = c->pp.ps;
+  ps.steps = m;
+  const S* src = (const S*)(c->ws + (c->cur ? c->L.fB : c->L.fA));
+  S* dst = (S*)(c->ws + (c->cur ? c->L.fA : c->L.fB));
+  unsigned* flags = (unsigned*)(c->ws + c->L.flags);
+  const dim3 grid(ps.ntx * ps.nty), block(c->pp.threads);
+  const size_t lds = patch_lds_values(c->p, ps) * sizeof(C);
+  if (needs_gen(c->p)) {
+    // the general free-energy kernel does not fit two FP64 nodes per thread
+    // in 128 registers: plan_patch gives it one
+    if constexpr (!(MODEL == MODEL_FE && NPT == 2 && sizeof(C) == 8))
+      hipLaunchKernelGGL((k_patch<MODEL, EOS, S, C, NPT, 1>), grid, block, lds, c->stream, src, dst,
+                         kp, ps, flags);
+  } else {
+    hipLaunchKernelGGL((k_patch<MODEL, EOS, S, C, NPT, 0>), grid, block, lds, c->stream, src, dst,
+                       kp, ps, flags);
+  }
+  c->cur ^= 1;
+}
+
+template <int MODEL, int EOS>
+void launch_patch_typed(lbm_ctx* c, int m) {
+  if (c->p.precision == LBM_FP64) {
+    if (c->pp.npt == 1) launch_patch<MODEL, EOS, double, double, 1>(c, c->kd, m);
+    else launch_patch<MODEL, EOS, double, double, 2>(c, c->kd, m);  // (FE: not GEN)
+  } else {
+    if (c->pp.npt == 1) launch_patch<MODEL, EOS, float, float, 1>(c, c->kf, m);
+    else launch_patch<MODEL, EOS, float, float, 2>(c, c->kf, m);
+  }
+}
+
+void step_patch(lbm_ctx* c, int m) {
+  if (c->p.model == LBM_MODEL_P) {
+    if (c->p.eos == LBM_EOS_CS) launch_patch_typed<MODEL_P, EOS_CS>(c, m);
+    else launch_patch_typed<MODEL_P, EOS_VDW>(c, m);
+  } else {
+    if (c->p.eos == LBM_EOS_CS) launch_patch_typed<MODEL_FE, EOS_CS>(c, m);
+    else launch_patch_typed<MODEL_FE, EOS_VDW>(c, m);
+  }
 }
 
 void step_twice(lbm_ctx* c) {
@@ -2705,6 +3190,8 @@ lbm_status observe_impl(lbm_ctx* c, int32_t cx, int32_t cy, lbm_obs* out,
 // Issue m steps: two per launch where the two-step kernel applies, else one.
 void advance(lbm_ctx* c, int m) {
   int k = 0;
+  if (c->pp.on)
+    for (; k < m; k += std::min(m - k, c->pp.ps.steps)) step_patch(c, std::min(m - k, c->pp.ps.steps));
   if (two_step_ok(c))
     for (; k + 2 <= m; k += 2) step_twice(c);
   for (; k < m; ++k) step_once(c);
@@ -2790,7 +3277,9 @@ lbm_status lbm_init(const lbm_params* p, void* d_workspace, size_t bytes,
   hipStream_t stream = (hipStream_t)hip_stream;
   std::vector<double> h;
   if ((st = read_host(d_rho0, (size_t)p->nx * p->ny, stream, h)) != LBM_OK) return st;
-  return ctx_setup(p, d_workspace, d_rho0, h, stream, out);
+  if ((st = ctx_setup(p, d_workspace, d_rho0, h, stream, out)) != LBM_OK) return st;
+  (*out)->pp = plan_patch(*p);
+  return LBM_OK;
 }
 
 lbm_status lbm_step(lbm_ctx* c, int64_t n) {
@@ -2799,6 +3288,15 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
   int64_t k = 0;
   while (k < n && st == LBM_OK) {
     const int64_t t = c->step + k;
+    if (c->pp.on) {
+      // as many steps as a launch takes, none across the drive's switch-on
+      int64_t m = std::min<int64_t>(n - k, c->pp.ps.steps);
+      if (c->p.ax != 0.0 && t < c->p.ax_from_step) m = std::min(m, c->p.ax_from_step - t);
+      set_drive(c, t);
+      step_patch(c, (int)m);
+      k += m;
+      continue;
+    }
     // a whole graph run needs the launch shape fixed (after the first
     // launch) and one drive state throughout
     const bool drive_const = c->p.ax == 0.0 || t >= c->p.ax_from_step ||
@@ -2865,6 +3363,14 @@ lbm_status lbm_destroy(lbm_ctx* c) {
 lbm_status lbm_launch_info(const lbm_ctx* c, lbm_launch* out) {
   if (!c || !out) return LBM_ERR_INVALID_ARG;
   memset(out, 0, sizeof(*out));
+  if (c->pp.on) {
+    out->steps_per_launch = c->pp.ps.steps;
+    out->strip = c->pp.ps.tx;
+    out->segment = c->pp.ps.ty;
+    out->workgroups = c->pp.ps.ntx * c->pp.ps.nty;
+    out->threads = c->pp.threads;
+    return LBM_OK;
+  }
   const bool two = two_step_ok(c);
   out->steps_per_launch = two ? 2 : 1;
   out->strip = two ? c->lc.bx2 : c->lc.bx;
@@ -2909,6 +3415,31 @@ lbm_status lbm_autotune(const lbm_params* p, void* d_workspace, size_t bytes,
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return LBM_ERR_HIP;
   double best_t = INFINITY;
   lbm_params bp = *p;
+  auto time_shape = [&](const lbm_params& q, bool patch) {
+    lbm_ctx* c = nullptr;
+    lbm_status r = ctx_setup(&q, d_workspace, d_rho0, h, stream, &c);
+    if (r != LBM_OK) return r;
+    if (patch) c->pp = plan_patch(q);
+    advance(c, 2);  // warm-up (and first-touch of the second buffer)
+    hipEventRecord(e0, stream);
+    advance(c, steps);
+    hipEventRecord(e1, stream);
+    if (hipEventSynchronize(e1) != hipSuccess) r = LBM_ERR_HIP;
+    float ms = 0.f;
+    hipEventElapsedTime(&ms, e0, e1);
+    delete c;
+    if (r == LBM_OK && ms / steps < best_t) {
+      best_t = ms / steps;
+      bp = q;
+    }
+    return r;
+  };
+  {
+    // the default launch shape, where that is patch launches
+    lbm_params q = *p;
+    q.tile_x = q.tile_y = q.kernel_flags = q.tile_rounds = 0;
+    if (plan_patch(q).on) st = time_shape(q, true);
+  }
   for (int bx : bxs) {
     if (bx == 256 && p->nx < 192) continue;
     for (int ly : lys) {
@@ -2918,22 +3449,7 @@ lbm_status lbm_autotune(const lbm_params* p, void* d_workspace, size_t bytes,
         q.tile_x = bx;
         q.tile_y = ly;
         q.kernel_flags = (int32_t)kf;
-        lbm_ctx* c = nullptr;
-        if ((st = ctx_setup(&q, d_workspace, d_rho0, h, stream, &c)) != LBM_OK) break;
-        advance(c, 2);  // warm-up (and first-touch of the second buffer)
-        hipEventRecord(e0, stream);
-        advance(c, steps);
-        hipEventRecord(e1, stream);
-        if (hipEventSynchronize(e1) != hipSuccess) st = LBM_ERR_HIP;
-        float ms = 0.f;
-        hipEventElapsedTime(&ms, e0, e1);
-        delete c;
-        if (st != LBM_OK) break;
-        double t = ms / steps;
-        if (t < best_t) {
-          best_t = t;
-          bp = q;
-        }
+        if ((st = time_shape(q, false)) != LBM_OK) break;
       }
     }
   }

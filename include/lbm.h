@@ -119,10 +119,10 @@ typedef struct {
   double rho_ref;       /* FP32_SHIFTED: reference density of the storage
                            shift (<= 0: the smallest initial density)       */
   /* Launch shape; 0 selects the tuned default (see lbm_autotune).  With all
-     of tile_x, tile_y, kernel_flags and tile_rounds 0 (and A = 0), a lattice
-     too small to fill the device with strips runs on patches: rectangular
-     tiles that take several steps per launch in LDS (lbm_launch_info shows
-     which).  Results do not depend on these, only the speed does. */
+     of tile_x, tile_y, kernel_flags and tile_rounds 0 (or LBM_KF_PATCH), and
+     A = 0, a lattice too small to fill the device with strips runs on
+     patches: rectangular tiles that take several steps per launch in LDS
+     (lbm_launch_info shows which).  Results do not depend on these, only the speed does. */
   int32_t tile_x;       /* columns per workgroup strip: 0, 64 or 256         */
   int32_t tile_y;       /* rows per workgroup segment: 1 .. 1024, or 0: set at
                            the first step so that the tiles fill whole rounds
@@ -170,6 +170,9 @@ typedef struct {
 #define LBM_KF_STRIP128 32u     /* the free-energy two-step kernel on
                                    128-column strips (the default)         */
 #define LBM_KF_STRIP192 64u     /* ... on 192-column strips                */
+#define LBM_KF_PATCH 128u       /* patches wherever the default launch shape
+                                   would take them; elsewhere as the other
+                                   fields say                              */
 #define LBM_KF_NO_XCD_REMAP 8u  /* keep the dispatch order of the tiles
                                    (default: a contiguous band of tiles per
                                    XCD, whose L2 the neighbours share)      */
@@ -253,7 +256,7 @@ lbm_status lbm_launch_info(const lbm_ctx* ctx, lbm_launch* out);
  * per launch and the two-step kernel's strip width), `steps` steps each, on
  * a scratch state started from d_rho0, and return the fastest in
  * best->tile_x / tile_y / kernel_flags (the other fields are copied from p;
- * all three 0: the default shape, where that is patches).
+ * patches: LBM_KF_PATCH, the tile fields then have no effect).
  * Uses d_workspace (lbm_workspace_bytes(p)); synchronises the stream; the
  * results of a run never depend on the choice, only its speed. */
 lbm_status lbm_autotune(const lbm_params* p, void* d_workspace, size_t bytes,

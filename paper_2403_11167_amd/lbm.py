@@ -28,6 +28,7 @@ BATCH_STALLED, BATCH_STALL_CHECKS = 5, 100
 KF_SET, KF_NT_STORE, KF_REGCAP, KF_PIPELINE, KF_NO_XCD_REMAP, KF_TWO_STEP, KF_STRIP128 = (
     0x80000000, 1, 2, 4, 8, 16, 32)
 KF_STRIP192 = 64
+KF_PATCH = 128
 
 EXPORTED_SYMBOLS = [
     "lbm_status_string", "lbm_workspace_bytes", "lbm_init", "lbm_step", "lbm_observe",

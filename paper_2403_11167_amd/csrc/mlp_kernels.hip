@@ -5,30 +5,31 @@
 // Adam (Kingma and Ba, 2015) on equilibria computed by the batched lattices.
 //
 // Kernels (gfx950):
-//   k_mlp_forward  tile of 16 samples per 256-thread workgroup; layer inputs
-//                  kept in LDS, weights streamed from L2 with reads that are
-//                  contiguous across the output index;
+//   k_mlp_forward  tiles of 16 samples, one wavefront per 16 columns of a
+//                  layer (eight per workgroup), the weights of its columns in
+//                  registers for every tile the workgroup walks;
 //   k_mlp_grad     forward, loss and back-propagation of a tile in one
 //                  workgroup; a workgroup walks several tiles and accumulates
-//                  its weight gradient in its own slice of the workspace; for
-//                  the transposed products the 128 x 128 weight matrix is
-//                  staged in LDS with rows padded to 129 words (no bank
-//                  conflicts); ~130 KB LDS per workgroup;
+//                  its weight gradient in its own slice of the workspace;
 //   k_mlp_reduce   sums the per-workgroup slices in a fixed order, so the
-//                  gradient is deterministic;
+//                  gradient is deterministic; in a training step it also
+//                  makes the Adam update;
 //   k_mlp_adam     one elementwise Adam update.
-// The network is ~34k parameters: every launch is latency-bound, not bound
-// by HBM or the matrix units.
+// The network is ~34k parameters and a training batch a few hundred samples,
+// so a step is bound by latency: the chain of layers, the memory round trips
+// and the launches.  All weights a wavefront needs (forward and transposed)
+// are therefore fetched at once when the kernel starts, and every contraction
+// runs on the matrix cores (mfma blocks of 16 samples by 16 columns), with
+// activations and errors passed through LDS between the layers.
 //
 // BF16 mode rounds every product operand (layer inputs and weights) to
 // bfloat16, round to nearest even; products of two bfloat16 values are exact
-// in FP32 and all sums accumulate in FP32.  Its two 128 x 128 hidden layers
-// run on the matrix cores (v_mfma_f32_16x16x16_bf16, hidden_mfma), in the
-// forward pass of inference and of training; the 4-wide input and output
-// layers and all FP32-mode products run on the vector ALUs.  Biases and
-// back-propagated errors are not rounded (so the backward products stay on
-// the vector ALUs in FP32); the weight rounding is treated as the identity
-// in the gradient.
+// in FP32 and all sums accumulate in FP32: its two hidden layers run as
+// v_mfma_f32_16x16x16_bf16.  Biases and back-propagated errors are not
+// rounded, so the backward products, like FP32 mode's hidden layers, run as
+// v_mfma_f32_16x16x4_f32, whose sum is the ascending chain of fused
+// multiply-adds of its four products (the same bits as an fmaf loop); the
+// weight rounding is treated as the identity in the gradient.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -51,9 +52,8 @@ constexpr int OFF_B4 = OFF_W4 + H * NO;
 constexpr int NPARAM = OFF_B4 + NO;
 static_assert(NPARAM == LBM_MLP_NPARAMS, "parameter count");
 constexpr int TS = 16;         // samples per tile
-constexpr int NT = 256;        // threads per workgroup
-constexpr int HALF = TS / 2;   // samples per thread in the 128-wide phases
-constexpr int WPAD = H + 1;    // padded LDS row
+constexpr int NT = 512;        // threads per workgroup: wavefront w has the columns 16 w ..
+constexpr int LP = H + 4;      // LDS row: 16 samples x 4 columns fall on 64 different banks
 constexpr int MAX_GRAD_BLOCKS = 128;
 
 struct Norm {
@@ -89,153 +89,285 @@ __device__ __forceinline__ short bf16_bits(float v) {
   return (short)(__float_as_uint(v) >> 16);
 }
 
-// One 128 -> 128 hidden layer of a 16-sample tile on the matrix cores
-// (BF16 mode): Z = A W + b with A the tile's rounded activations [16][128]
-// and W the layer's weights [128][128] (row k, column j), rounded to
-// bfloat16 as they are read; products of bfloat16 values are exact and the
-// sums accumulate in FP32.  v_mfma_f32_16x16x16_bf16 multiplies a 16 x 16
-// block of A by a 16 x 16 block of W: lane l supplies A[l % 16][4 (l / 16)
-// + v] and W[4 (l / 16) + v][l % 16] (v = 0..3, offsets within the blocks)
-// and receives Z[4 (l / 16) + v][l % 16].  Each of the four wavefronts
-// computes two 16-column blocks of Z over the eight 16-row blocks of W.
-__device__ __forceinline__ void hidden_mfma(const float* __restrict__ W, const float* __restrict__ bias,
-                            const float (*a)[H], float (*z)[H], float (*an)[H]) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int r = lane & 15, q = lane >> 4;
+// Matrix-core blocks of 16 x 16 (lane l: r = l % 16, q = l / 16).
+// v_mfma_f32_16x16x16_bf16: lane l supplies A[r][4 q + v] and B[4 q + v][r];
+// v_mfma_f32_16x16x4_f32: A[r][q] and B[q][r]; both receive D[4 q + v][r]
+// (v = 0..3).  A tile's rows are its samples, so lane l of wavefront w holds
+// samples 4 q + v of column 16 w + r of every layer.
+struct Lane {
+  int r, q, j;  // j: the lane's column
+  __device__ __forceinline__ Lane() {
+    const int l = threadIdx.x & 63;
+    r = l & 15;
+    q = l >> 4;
+    j = 16 * (threadIdx.x >> 6) + r;
+  }
+};
+
+// Wait for a matrix-core result before it is used across a branch: the
+// hardware needs 11 wait states from a 16x16x4 FP32 mfma to a store that reads
+// its result, and the compiler counted none where a branch lay between the two
+// (stores of stale values).
+__device__ __forceinline__ void mfma_settle(f32x4& v) {
+  asm volatile("s_nop 7\n\ts_nop 7" : "+v"(v));
+}
+
+// A 128 x 128 weight matrix as the workgroup fetches it: thread t has float4s
+// t, t + NT, ... of its 4096, so that every access is a whole line (fetched in
+// operand order, lane by lane, the two matrices took 17 us of a 28 us
+// gradient); stage() rounds it into LDS, whose rows are LP long: the operands
+// of the BF16 forward product (rows 4 q + v, columns r) and of the transposed
+// one (rows r, columns 4 kk + q) then fall on 64 different banks.
+constexpr int W4T = H * H / 4 / NT;
+struct Mat {
+  f32x4 w[W4T];
+  __device__ __forceinline__ void fetch(const float* __restrict__ W) {
+    if (((uintptr_t)W & 15) == 0) {
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb) {
-    const int j = (2 * wv + nb) * 16 + r;
-    const float b = bias[j];
+      for (int i = 0; i < W4T; ++i) w[i] = ((const f32x4*)W)[threadIdx.x + i * NT];
+    } else {  // parameters that start inside a caller's larger buffer
+#pragma unroll
+      for (int i = 0; i < W4T; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) w[i][v] = W[4 * (threadIdx.x + i * NT) + v];
+    }
+  }
+  template <int BF>
+  __device__ __forceinline__ void stage(float (*s_w)[LP]) const {
+#pragma unroll
+    for (int i = 0; i < W4T; ++i) {
+      const int e = threadIdx.x + i * NT;
+      f32x4 x;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[v] = rnd<BF>(w[i][v]);
+      *(f32x4*)&s_w[e / (H / 4)][4 * (e % (H / 4))] = x;
+    }
+  }
+};
+
+// A hidden layer's staged weights for the wavefront's columns, in operand
+// order, and the product a W + b of a tile with them.
+template <int BF>
+struct FwdW;
+template <>
+struct FwdW<1> {
+  bf16x4 w[H / 16];
+  __device__ __forceinline__ void read(const float (*s_w)[LP], const Lane& n) {
+#pragma unroll
+    for (int kb = 0; kb < H / 16; ++kb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) w[kb][v] = bf16_bits(s_w[kb * 16 + 4 * n.q + v][n.j]);
+  }
+  __device__ __forceinline__ f32x4 run(const float (*a)[LP], float b, const Lane& n) const {
     f32x4 acc = {b, b, b, b};
 #pragma unroll
     for (int kb = 0; kb < H / 16; ++kb) {
-      const int k0 = kb * 16 + 4 * q;
-      bf16x4 av, wv4;
+      const f32x4 x = *(const f32x4*)&a[n.r][kb * 16 + 4 * n.q];
+      bf16x4 av;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        av[v] = bf16_bits(a[r][k0 + v]);
-        wv4[v] = bf16_bits(bf16r(W[(k0 + v) * H + j]));
-      }
-      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, wv4, acc, 0, 0, 0);
+      for (int v = 0; v < 4; ++v) av[v] = bf16_bits(x[v]);
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, w[kb], acc, 0, 0, 0);
     }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = 4 * q + v;
-      z[i][j] = acc[v];
-      an[i][j] = bf16r(gelu(acc[v]));
-    }
+    mfma_settle(acc);
+    return acc;
   }
+};
+template <>
+struct FwdW<0> {
+  float w[H / 4];
+  __device__ __forceinline__ void read(const float (*s_w)[LP], const Lane& n) {
+#pragma unroll
+    for (int kk = 0; kk < H / 4; ++kk) w[kk] = s_w[4 * kk + n.q][n.j];
+  }
+  __device__ __forceinline__ f32x4 run(const float (*a)[LP], float b, const Lane& n) const {
+    f32x4 acc = {b, b, b, b};
+#pragma unroll
+    for (int kk = 0; kk < H / 4; ++kk)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[n.r][4 * kk + n.q], w[kk], acc, 0, 0, 0);
+    mfma_settle(acc);
+    return acc;
+  }
+};
+
+// The rest of a lane's forward weights: its column of the input layer, the
+// biases of its columns (b4: of output r % NO).
+template <int BF>
+struct Net {
+  float w1[NI], b1, b2, b3, b4;
+  __device__ __forceinline__ void load(const float* __restrict__ P, const Lane& n) {
+#pragma unroll
+    for (int k = 0; k < NI; ++k) w1[k] = rnd<BF>(P[OFF_W1 + k * H + n.j]);
+    b1 = P[OFF_B1 + n.j];
+    b2 = P[OFF_B2 + n.j];
+    b3 = P[OFF_B3 + n.j];
+    b4 = P[OFF_B4 + (n.r & (NO - 1))];
+  }
+};
+
+// The output layer's weights, rounded, into LDS (visible after a barrier).
+template <int BF>
+__device__ __forceinline__ void stage_w4(const float* __restrict__ P, float (*s_w4)[NO]) {
+  s_w4[threadIdx.x / NO][threadIdx.x % NO] = rnd<BF>(P[OFF_W4 + threadIdx.x]);  // NT = H NO
 }
 
-// Forward pass of one tile.  s_a0: [TS][NI] rounded inputs (already set);
-// s_z: [3][TS][H] pre-activations; s_a: [3][TS][H] rounded activations;
-// s_o: [TS][NO] outputs in normalised log space.  Sample rows >= nv hold
-// zero inputs and finite values that the callers ignore.
+// The layers of a tile's forward pass: z the lane's pre-activations (kept for
+// the derivative), the rounded activations to LDS.  Sample rows without a
+// sample hold zero inputs and finite values that the callers ignore.
 template <int BF>
-__device__ __forceinline__ void forward_tile(const float* __restrict__ P, const float (*s_a0)[NI],
-                             float (*s_z)[TS][H], float (*s_a)[TS][H], float (*s_o)[NO]) {
-  const int t = threadIdx.x;
-  const int j = t & (H - 1), sh = (t >> 7) * HALF;
-  {
-    float acc[HALF];
-    const float b = P[OFF_B1 + j];
+__device__ __forceinline__ void activate(const f32x4& z, const Lane& n, float (*a)[LP]) {
 #pragma unroll
-    for (int q = 0; q < HALF; ++q) acc[q] = b;
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-      const float w = rnd<BF>(P[OFF_W1 + k * H + j]);
-#pragma unroll
-      for (int q = 0; q < HALF; ++q) acc[q] = fmaf(w, s_a0[sh + q][k], acc[q]);
-    }
-#pragma unroll
-    for (int q = 0; q < HALF; ++q) {
-      s_z[0][sh + q][j] = acc[q];
-      s_a[0][sh + q][j] = rnd<BF>(gelu(acc[q]));
-    }
-  }
-  __syncthreads();
-  for (int l = 1; l < 3; ++l) {
-    const float* W = P + (l == 1 ? OFF_W2 : OFF_W3);
-    if constexpr (BF) {
-      hidden_mfma(W, P + (l == 1 ? OFF_B2 : OFF_B3), s_a[l - 1], s_z[l], s_a[l]);
-      __syncthreads();
-      continue;
-    }
-    float acc[HALF];
-    const float b = P[(l == 1 ? OFF_B2 : OFF_B3) + j];
-#pragma unroll
-    for (int q = 0; q < HALF; ++q) acc[q] = b;
-    for (int k = 0; k < H; ++k) {
-      const float w = rnd<BF>(W[k * H + j]);
-#pragma unroll
-      for (int q = 0; q < HALF; ++q) acc[q] = fmaf(w, s_a[l - 1][sh + q][k], acc[q]);
-    }
-#pragma unroll
-    for (int q = 0; q < HALF; ++q) {
-      s_z[l][sh + q][j] = acc[q];
-      s_a[l][sh + q][j] = rnd<BF>(gelu(acc[q]));
-    }
-    __syncthreads();
-  }
-  if (t < TS * NO) {
-    const int s = t / NO, o = t % NO;
-    float acc = P[OFF_B4 + o];
-    for (int k = 0; k < H; ++k) acc = fmaf(rnd<BF>(P[OFF_W4 + k * NO + o]), s_a[2][s][k], acc);
-    s_o[s][o] = acc;
-  }
-  __syncthreads();
+  for (int v = 0; v < 4; ++v) a[4 * n.q + v][n.j] = rnd<BF>(gelu(z[v]));
 }
 
 template <int BF>
-__device__ __forceinline__ void load_inputs(const float* __restrict__ X, const Norm& nm, int s0,
-                                            int nv, float (*s_a0)[NI], const int* __restrict__ idx,
-                                            int nrows, bool* bad) {
-  const int t = threadIdx.x;
-  if (t < TS * NI) {
-    const int s = t / NI, k = t % NI;
-    float v = 0.0f;
-    if (s < nv) {
-      const int r = idx ? idx[s0 + s] : s0 + s;
-      if (r >= 0 && r < nrows) v = rnd<BF>((X[(size_t)r * NI + k] - nm.xs[k]) * nm.xk[k]);
-      else *bad = true;
-    }
-    s_a0[s][k] = v;
+__device__ __forceinline__ f32x4 input_layer(const Net<BF>& net, const Lane& n,
+                                             const float (*s_a0)[NI]) {
+  f32x4 z;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    float acc = net.b1;
+#pragma unroll
+    for (int k = 0; k < NI; ++k) acc = fmaf(net.w1[k], s_a0[4 * n.q + v][k], acc);
+    z[v] = acc;
   }
+  return z;
 }
 
+// Outputs in normalised log space, by wavefront 0 (visible to it; the others
+// need a barrier).
+__device__ __forceinline__ void output_layer(const float (*a)[LP], const float (*s_w4)[NO],
+                                             float b4, const Lane& n, float (*s_o)[NO]) {
+  if (threadIdx.x >= 64) return;
+  // (columns r >= NO repeat the first ones and are dropped)
+  f32x4 acc = {b4, b4, b4, b4};
+#pragma unroll
+  for (int kk = 0; kk < H / 4; ++kk)
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[n.r][4 * kk + n.q],
+                                               s_w4[4 * kk + n.q][n.r & (NO - 1)], acc, 0, 0, 0);
+  mfma_settle(acc);
+  if (n.r < NO)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s_o[4 * n.q + v][n.r] = acc[v];
+}
+
+// Predictions, a workgroup walking tiles with a stride of the grid.  256
+// samples (16 workgroups): 7.5 us (12.5 us with the weights read from L2 inside
+// the products).
 template <int BF>
 __global__ __launch_bounds__(NT) void k_mlp_forward(const float* __restrict__ P, Norm nm,
                                                     const float* __restrict__ X, int n,
                                                     float* __restrict__ Y) {
   __shared__ float s_a0[TS][NI];
-  __shared__ float s_z[3][TS][H];
-  __shared__ float s_a[3][TS][H];
-  __shared__ float s_o[TS][NO];
-  const int s0 = blockIdx.x * TS;
-  const int nv = min(TS, n - s0);
-  bool bad = false;
-  load_inputs<BF>(X, nm, s0, nv, s_a0, nullptr, n, &bad);
-  __syncthreads();
-  forward_tile<BF>(P, s_a0, s_z, s_a, s_o);
+  __shared__ __attribute__((aligned(16))) float s_a[3][TS][LP];
+  __shared__ __attribute__((aligned(16))) float s_w[H][LP];
+  __shared__ float s_o[TS][NO], s_w4[H][NO];
   const int t = threadIdx.x;
-  if (t < TS * NO) {
-    const int s = t / NO, o = t % NO;
-    if (s < nv) Y[(size_t)(s0 + s) * NO + o] = expf(s_o[s][o] * nm.yk[o] + nm.ys[o]);
+  const Lane ln;
+  FwdW<BF> l2, l3;
+  Net<BF> net;
+  {
+    Mat m2, m3;
+    m2.fetch(P + OFF_W2);
+    m3.fetch(P + OFF_W3);
+    net.load(P, ln);
+    stage_w4<BF>(P, s_w4);
+    m2.template stage<BF>(s_w);
+    __syncthreads();
+    l2.read(s_w, ln);
+    __syncthreads();
+    m3.template stage<BF>(s_w);
+    __syncthreads();
+    l3.read(s_w, ln);
+  }
+  const int ntiles = (n + TS - 1) / TS;
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int s = t / NI, k = t % NI;
+    const int row = tile * TS + s;
+    if (t < TS * NI)
+      s_a0[s][k] = row < n ? rnd<BF>((X[(size_t)row * NI + k] - nm.xs[k]) * nm.xk[k]) : 0.0f;
+    __syncthreads();
+    activate<BF>(input_layer(net, ln, s_a0), ln, s_a[0]);
+    __syncthreads();
+    activate<BF>(l2.run(s_a[0], net.b2, ln), ln, s_a[1]);
+    __syncthreads();
+    activate<BF>(l3.run(s_a[1], net.b3, ln), ln, s_a[2]);
+    __syncthreads();
+    output_layer(s_a[2], s_w4, net.b4, ln, s_o);
+    if (t < TS * NO && row < n)  // wavefront 0, which wrote s_o (NI = NO)
+      Y[(size_t)row * NO + k] = expf(s_o[s][k] * nm.yk[k] + nm.ys[k]);
+    // (wavefront 0 alone writes s_a0 of the next tile before the next barrier,
+    // and every wavefront has read this tile's before the last one)
   }
 }
 
 // Gradient slice update: the first tile of a workgroup stores, later tiles
 // add.  Each slice element is owned by one thread in every phase, the same
 // thread for every tile.
-__device__ __forceinline__ void gput(float* p, float g, bool first) {
+template <class V>
+__device__ __forceinline__ void gput(V* p, V g, bool first) {
   if (first) *p = g;
   else *p += g;
+}
+
+// Weight gradient of a hidden layer, dW[k][j] = sum_s a[s][k] d[s][j] (the
+// wavefront's columns j as the rows of the block, so that a lane gets four
+// consecutive j of one k), and its bias gradient.
+__device__ __forceinline__ void hidden_grad(const float (*a)[LP], const float (*d)[LP],
+                                            const Lane& n, float* __restrict__ GW,
+                                            float* __restrict__ GB, bool first) {
+  const int jb = n.j - n.r;
+  float dj[TS / 4], ak[H / 16][TS / 4];
+#pragma unroll
+  for (int ss = 0; ss < TS / 4; ++ss) {
+    dj[ss] = d[4 * ss + n.q][n.j];
+#pragma unroll
+    for (int kb = 0; kb < H / 16; ++kb) ak[kb][ss] = a[4 * ss + n.q][16 * kb + n.r];
+  }
+  f32x4 g[H / 16];
+#pragma unroll
+  for (int kb = 0; kb < H / 16; ++kb) g[kb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  // (the chains of the eight blocks interleaved: each waits for itself only)
+#pragma unroll
+  for (int ss = 0; ss < TS / 4; ++ss)
+#pragma unroll
+    for (int kb = 0; kb < H / 16; ++kb)
+      g[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(dj[ss], ak[kb][ss], g[kb], 0, 0, 0);
+  asm volatile("s_nop 7\n\ts_nop 7"  // mfma_settle of all eight
+               : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]), "+v"(g[4]), "+v"(g[5]),
+                 "+v"(g[6]), "+v"(g[7]));
+  static_assert(H / 16 == 8, "blocks settled");
+#pragma unroll
+  for (int kb = 0; kb < H / 16; ++kb) {
+    gput((f32x4*)&GW[(16 * kb + n.r) * H + jb + 4 * n.q], g[kb], first);
+  }
+  if (threadIdx.x < H) {
+    float b = 0.0f;
+#pragma unroll
+    for (int s = 0; s < TS; ++s) b += d[s][threadIdx.x];
+    gput(&GB[threadIdx.x], b, first);
+  }
+}
+
+// Transposed product of a hidden layer with staged weights: (d W^T)[s][k] for
+// the wavefront's columns k.
+__device__ __forceinline__ f32x4 hidden_back(const float (*d)[LP], const float (*s_w)[LP],
+                                             const Lane& n) {
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int kk = 0; kk < H / 4; ++kk)
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(d[n.r][4 * kk + n.q], s_w[n.j][4 * kk + n.q], acc,
+                                               0, 0, 0);
+  mfma_settle(acc);
+  return acc;
 }
 
 // Loss and gradient partials.  Workgroup g handles tiles g, g + G, ...
 // (G <= number of tiles, so every workgroup has at least one); its gradient
 // slice part[g * NPARAM ...] and loss partial lpart[g] are fully written by
-// this kernel (no prior clearing needed).
+// this kernel (no prior clearing needed).  256 samples (16 workgroups): 17 us
+// (58 us with the backward products on the vector ALUs); four products of 2048
+// cycles each on the FP32 matrix cores of one CU are 3.5 us of it, the rest
+// the fetch of the weights and the chain of layers.
 template <int BF>
 __global__ __launch_bounds__(NT) void k_mlp_grad(const float* __restrict__ P, Norm nm,
                                                  const float* __restrict__ X,
@@ -244,157 +376,176 @@ __global__ __launch_bounds__(NT) void k_mlp_grad(const float* __restrict__ P, No
                                                  float scale, float* __restrict__ part,
                                                  float* __restrict__ lpart) {
   __shared__ float s_a0[TS][NI];
-  __shared__ float s_z[3][TS][H];
-  __shared__ float s_a[3][TS][H];
-  __shared__ float s_d[TS][H];   // dL/dz of the current layer
-  __shared__ float s_e[TS][H];   // dL/dz of the layer below
-  __shared__ float s_w[H][WPAD];
-  __shared__ float s_o[TS][NO];  // outputs, then dL/dout
-  __shared__ float s_l[NT / 64];
+  __shared__ __attribute__((aligned(16))) float s_a[3][TS][LP];
+  __shared__ __attribute__((aligned(16))) float s_w[H][LP];
+  __shared__ float s_d[TS][LP];   // dL/dz of layers 3 and 1
+  __shared__ float s_e[TS][LP];   // dL/dz of layer 2
+  __shared__ __attribute__((aligned(16))) float s_o[TS][NO];  // outputs, then dL/dout
+  __shared__ __attribute__((aligned(16))) float s_w4[H][NO];
   __shared__ int s_bad;
   const int t = threadIdx.x;
-  const int j = t & (H - 1), hsel = t >> 7, sh = hsel * HALF;
-  float* G = part + (size_t)blockIdx.x * NPARAM;
+  Lane ln;
   if (t == 0) s_bad = 0;
+  Mat m2, m3;
+  m2.fetch(P + OFF_W2);
+  m3.fetch(P + OFF_W3);
+  Net<BF> net;
+  net.load(P, ln);
+  stage_w4<BF>(P, s_w4);
   __syncthreads();
   float lacc = 0.0f;
   const int ntiles = (n + TS - 1) / TS;
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int s0 = tile * TS;
-    const int nv = min(TS, n - s0);
+    // addresses formed anew for each tile: hoisted out of the loop they take
+    // the registers that the weights are in
+    asm volatile("" : "+v"(ln.r), "+v"(ln.q), "+v"(ln.j));
+    int slice = blockIdx.x * NPARAM;
+    asm volatile("" : "+s"(slice));
+    float* const G = part + slice;
     const bool first = tile == (int)blockIdx.x;
-    bool bad = false;
-    load_inputs<BF>(X, nm, s0, nv, s_a0, idx, nrows, &bad);
-    if (bad) s_bad = 1;
-    __syncthreads();
-    forward_tile<BF>(P, s_a0, s_z, s_a, s_o);
-    // loss and dL/dout (zero for padding rows and rejected indices)
-    float dv = 0.0f;
-    if (t < TS * NO) {
-      const int s = t / NO, o = t % NO;
-      if (s < nv) {
-        const int r = idx ? idx[s0 + s] : s0 + s;
+    // wavefront 0: input k and target k of sample s (NI = NO)
+    const int s = t / NI, k = t % NI;
+    bool valid = false;
+    float yv = 1.0f;
+    if (t < TS * NI) {
+      float v = 0.0f;
+      if (tile * TS + s < n) {
+        const int r = idx ? idx[tile * TS + s] : tile * TS + s;
         if (r >= 0 && r < nrows) {
-          const float tgt = (logf(Y[(size_t)r * NO + o]) - nm.ys[o]) / nm.yk[o];
-          const float res = s_o[s][o] - tgt;
-          lacc = fmaf(res, res, lacc);
-          dv = 2.0f * res * scale;
+          valid = true;
+          v = rnd<BF>((X[(size_t)r * NI + k] - nm.xs[k]) * nm.xk[k]);
+          yv = Y[(size_t)r * NO + k];
+        } else {
+          s_bad = 1;
         }
       }
+      s_a0[s][k] = v;
     }
-    __syncthreads();  // every output read before it is overwritten
-    if (t < TS * NO) s_o[t / NO][t % NO] = dv;
+    m2.template stage<BF>(s_w);
+    __syncthreads();
+    f32x4 z[3];
+    FwdW<BF> lw;
+    lw.read(s_w, ln);
+    z[0] = input_layer(net, ln, s_a0);
+    activate<BF>(z[0], ln, s_a[0]);
+    __syncthreads();
+    m3.template stage<BF>(s_w);
+    z[1] = lw.run(s_a[0], net.b2, ln);
+    activate<BF>(z[1], ln, s_a[1]);
+    __syncthreads();
+    lw.read(s_w, ln);
+    z[2] = lw.run(s_a[1], net.b3, ln);
+    activate<BF>(z[2], ln, s_a[2]);
+    __syncthreads();
+    output_layer(s_a[2], s_w4, net.b4, ln, s_o);
+    // loss and dL/dout (zero for padding rows and rejected indices), by
+    // wavefront 0, which wrote the outputs
+    if (t < TS * NO) {
+      float dv = 0.0f;
+      if (valid) {
+        const float tgt = (logf(yv) - nm.ys[k]) / nm.yk[k];
+        const float res = s_o[s][k] - tgt;
+        lacc = fmaf(res, res, lacc);
+        dv = 2.0f * res * scale;
+      }
+      s_o[s][k] = dv;
+    }
     __syncthreads();
     // output layer: dW4[k][o] = sum_s a3[s][k] dout[s][o]
-    for (int e = t; e < H * NO; e += NT) {
-      const int k = e / NO, o = e % NO;
-      float g = 0.0f;
-#pragma unroll
-      for (int s = 0; s < TS; ++s) g = fmaf(s_a[2][s][k], s_o[s][o], g);
-      gput(&G[OFF_W4 + e], g, first);
-    }
-    if (t < NO) {
-      float g = 0.0f;
-#pragma unroll
-      for (int s = 0; s < TS; ++s) g += s_o[s][t];
-      gput(&G[OFF_B4 + t], g, first);
-    }
     {
-      float w[NO];
+      const f32x4 w4 = *(const f32x4*)s_w4[ln.j];
 #pragma unroll
-      for (int o = 0; o < NO; ++o) w[o] = rnd<BF>(P[OFF_W4 + j * NO + o]);
-#pragma unroll
-      for (int q = 0; q < HALF; ++q) {
-        const int s = sh + q;
+      for (int v = 0; v < 4; ++v) {
+        const f32x4 dv = *(const f32x4*)s_o[4 * ln.q + v];
         float da = 0.0f;
 #pragma unroll
-        for (int o = 0; o < NO; ++o) da = fmaf(s_o[s][o], w[o], da);
-        s_d[s][j] = da * gelu_d(s_z[2][s][j]);
+        for (int o = 0; o < NO; ++o) da = fmaf(dv[o], w4[o], da);
+        s_d[4 * ln.q + v][ln.j] = da * gelu_d(z[2][v]);
+      }
+      float g = 0.0f;  // NT = H NO elements
+#pragma unroll
+      for (int i = 0; i < TS; ++i) g = fmaf(s_a[2][i][t / NO], s_o[i][t % NO], g);
+      gput(&G[OFF_W4 + t], g, first);
+      if (t < NO) {
+        float b = 0.0f;
+#pragma unroll
+        for (int i = 0; i < TS; ++i) b += s_o[i][t];
+        gput(&G[OFF_B4 + t], b, first);
       }
     }
     __syncthreads();
-    // hidden layers 3 and 2: input activations s_a[l - 1], weights W_{l+1}
-    for (int l = 2; l >= 1; --l) {
-      const int offw = (l == 2) ? OFF_W3 : OFF_W2;
-      const int offb = (l == 2) ? OFF_B3 : OFF_B2;
-      const float* W = P + offw;
-      for (int e = t; e < H * H; e += NT) s_w[e >> 7][e & (H - 1)] = rnd<BF>(W[e]);
-      {
-        float dz[TS];
+    // hidden layers 3 and 2
+    {
+      const f32x4 e = hidden_back(s_d, s_w, ln);
 #pragma unroll
-        for (int s = 0; s < TS; ++s) dz[s] = s_d[s][j];
-        for (int m = 0; m < H / 2; ++m) {
-          const int k = hsel + 2 * m;
-          float g = 0.0f;
-#pragma unroll
-          for (int s = 0; s < TS; ++s) g = fmaf(s_a[l - 1][s][k], dz[s], g);
-          gput(&G[offw + k * H + j], g, first);
-        }
-        if (hsel == 0) {
-          float g = 0.0f;
-#pragma unroll
-          for (int s = 0; s < TS; ++s) g += dz[s];
-          gput(&G[offb + j], g, first);
-        }
-      }
-      __syncthreads();  // weights staged
-      {
-        float acc[HALF];
-#pragma unroll
-        for (int q = 0; q < HALF; ++q) acc[q] = 0.0f;
-        for (int jj = 0; jj < H; ++jj) {
-          const float w = s_w[j][jj];
-#pragma unroll
-          for (int q = 0; q < HALF; ++q) acc[q] = fmaf(s_d[sh + q][jj], w, acc[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < HALF; ++q) s_e[sh + q][j] = acc[q] * gelu_d(s_z[l - 1][sh + q][j]);
-      }
-      __syncthreads();
-      for (int e = t; e < TS * H; e += NT) s_d[e >> 7][e & (H - 1)] = s_e[e >> 7][e & (H - 1)];
-      __syncthreads();
+      for (int v = 0; v < 4; ++v) s_e[4 * ln.q + v][ln.j] = e[v] * gelu_d(z[1][v]);
+      hidden_grad(s_a[1], s_d, ln, G + OFF_W3, G + OFF_B3, first);
     }
+    __syncthreads();
+    m2.template stage<BF>(s_w);
+    __syncthreads();
+    {
+      const f32x4 e = hidden_back(s_e, s_w, ln);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s_d[4 * ln.q + v][ln.j] = e[v] * gelu_d(z[0][v]);
+      hidden_grad(s_a[0], s_e, ln, G + OFF_W2, G + OFF_B2, first);
+    }
+    __syncthreads();
     // first layer: dW1[k][j] = sum_s a0[s][k] dz1[s][j]
     {
-      float dz[TS];
+      const int k1 = t >> 7, j = t & (H - 1);  // NT = NI H elements
+      float g = 0.0f;
 #pragma unroll
-      for (int s = 0; s < TS; ++s) dz[s] = s_d[s][j];
+      for (int i = 0; i < TS; ++i) g = fmaf(s_a0[i][k1], s_d[i][j], g);
+      gput(&G[OFF_W1 + t], g, first);
+      if (k1 == 0) {
+        float b = 0.0f;
 #pragma unroll
-      for (int m = 0; m < NI / 2; ++m) {
-        const int k = hsel + 2 * m;
-        float g = 0.0f;
-#pragma unroll
-        for (int s = 0; s < TS; ++s) g = fmaf(s_a0[s][k], dz[s], g);
-        gput(&G[OFF_W1 + k * H + j], g, first);
-      }
-      if (hsel == 0) {
-        float g = 0.0f;
-#pragma unroll
-        for (int s = 0; s < TS; ++s) g += dz[s];
-        gput(&G[OFF_B1 + j], g, first);
+        for (int i = 0; i < TS; ++i) b += s_d[i][j];
+        gput(&G[OFF_B1 + j], b, first);
       }
     }
     __syncthreads();  // LDS reused by the next tile
   }
-  // loss partial of this workgroup
-  for (int off = 32; off > 0; off >>= 1) lacc += __shfl_down(lacc, off, 64);
-  if ((t & 63) == 0) s_l[t >> 6] = lacc;
-  __syncthreads();
-  if (t == 0) {
-    float s = 0.0f;
-    for (int w = 0; w < NT / 64; ++w) s += s_l[w];
-    lpart[blockIdx.x] = s_bad ? NAN : s;
+  // loss partial of this workgroup (wavefront 0 holds it)
+  if (t < 64) {
+    for (int off = 32; off > 0; off >>= 1) lacc += __shfl_down(lacc, off, 64);
+    if (t == 0) lpart[blockIdx.x] = s_bad ? NAN : lacc;
   }
 }
+static_assert(NI == NO && TS * NI == 64, "wavefront 0 holds a tile's inputs and targets");
+static_assert(NT == H * NO && NT == NI * H && NT == 4 * H, "element per thread phases");
 
+__device__ __forceinline__ void adam_update(float* __restrict__ P, float* __restrict__ M,
+                                            float* __restrict__ V, int p, float g, float lr,
+                                            float b1, float b2, float eps, float bc1, float bc2) {
+  const float m = b1 * M[p] + (1.0f - b1) * g;
+  const float v = b2 * V[p] + (1.0f - b2) * g * g;
+  M[p] = m;
+  V[p] = v;
+  P[p] -= lr * (m / bc1) / (sqrtf(v / bc2) + eps);
+}
+
+struct Adam {
+  float *P, *M, *V;
+  float lr, b1, b2, eps, bc1, bc2;
+};
+
+// Gradient from the slices, in their order; ADAM = 1: and the update of the
+// parameters with it (a training step saves the launch and the gradient's
+// round trip).
+template <int ADAM>
 __global__ void k_mlp_reduce(const float* __restrict__ part, const float* __restrict__ lpart,
                              int nblk, float scale, float* __restrict__ grad,
-                             float* __restrict__ loss) {
+                             float* __restrict__ loss, const Adam ad) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p < NPARAM) {
     float g = 0.0f;
+#pragma unroll 8
     for (int b = 0; b < nblk; ++b) g += part[(size_t)b * NPARAM + p];
     grad[p] = g;
+    if constexpr (ADAM)
+      adam_update(ad.P, ad.M, ad.V, p, g, ad.lr, ad.b1, ad.b2, ad.eps, ad.bc1, ad.bc2);
   }
   if (p == 0 && loss) {
     float s = 0.0f;
@@ -403,17 +554,10 @@ __global__ void k_mlp_reduce(const float* __restrict__ part, const float* __rest
   }
 }
 
-__global__ void k_mlp_adam(float* __restrict__ P, float* __restrict__ M, float* __restrict__ V,
-                           const float* __restrict__ G, float lr, float b1, float b2, float eps,
-                           float bc1, float bc2) {
+__global__ void k_mlp_adam(const float* __restrict__ G, const Adam ad) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= NPARAM) return;
-  const float g = G[p];
-  const float m = b1 * M[p] + (1.0f - b1) * g;
-  const float v = b2 * V[p] + (1.0f - b2) * g * g;
-  M[p] = m;
-  V[p] = v;
-  P[p] -= lr * (m / bc1) / (sqrtf(v / bc2) + eps);
+  if (p < NPARAM)
+    adam_update(ad.P, ad.M, ad.V, p, G[p], ad.lr, ad.b1, ad.b2, ad.eps, ad.bc1, ad.bc2);
 }
 
 Norm to_norm(const lbm_mlp_norm* n) {
@@ -459,11 +603,31 @@ lbm_status grad_args_ok(const float* d_params, const lbm_mlp_norm* norm, const f
   return LBM_OK;
 }
 
+// The same with a caller workspace.
+lbm_status grad_ws_ok(const float* d_params, const lbm_mlp_norm* norm, const float* d_x,
+                      const float* d_y, int32_t n_rows, const int32_t* d_idx, int32_t n,
+                      const float* d_grad, int32_t flags, const void* ws, size_t bytes) {
+  const lbm_status s = grad_args_ok(d_params, norm, d_x, d_y, n_rows, d_idx, n, d_grad, flags);
+  if (s != LBM_OK) return s;
+  const int g = grad_blocks(n);
+  const size_t need = part_bytes(g) + align256((size_t)g * sizeof(float));
+  if (!ws || bytes < need || ((uintptr_t)ws % 256) != 0) return LBM_ERR_WORKSPACE;
+  return LBM_OK;
+}
+
+Adam make_adam(float* d_params, float* d_m, float* d_v, int64_t t, float lr, float b1, float b2,
+               float eps) {
+  const float bc1 = (float)(1.0 - pow((double)b1, (double)t));
+  const float bc2 = (float)(1.0 - pow((double)b2, (double)t));
+  return Adam{d_params, d_m, d_v, lr, b1, b2, eps, bc1, bc2};
+}
+
 // The gradient kernels of lbm_mlp_grad on a scratch area `ws` laid out as
-// above (arguments already checked).
+// above (arguments already checked), with the Adam update if one is given.
 lbm_status grad_launch(const float* d_params, const lbm_mlp_norm* norm, const float* d_x,
                        const float* d_y, int32_t n_rows, const int32_t* d_idx, int32_t n,
-                       float* d_grad, float* d_loss, int32_t flags, char* ws, hipStream_t st) {
+                       float* d_grad, float* d_loss, int32_t flags, char* ws, hipStream_t st,
+                       const Adam* adam = nullptr) {
   const Norm nm = to_norm(norm);
   const int g = grad_blocks(n);
   float* part = (float*)ws;
@@ -475,8 +639,11 @@ lbm_status grad_launch(const float* d_params, const lbm_mlp_norm* norm, const fl
   else
     hipLaunchKernelGGL(k_mlp_grad<0>, dim3(g), dim3(NT), 0, st, d_params, nm, d_x, d_y, d_idx,
                        n, n_rows, scale, part, lpart);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((NPARAM + 255) / 256), dim3(256), 0, st, part, lpart, g,
-                     scale, d_grad, d_loss);
+  const dim3 rg((NPARAM + 255) / 256), rb(256);
+  if (adam)
+    hipLaunchKernelGGL(k_mlp_reduce<1>, rg, rb, 0, st, part, lpart, g, scale, d_grad, d_loss, *adam);
+  else
+    hipLaunchKernelGGL(k_mlp_reduce<0>, rg, rb, 0, st, part, lpart, g, scale, d_grad, d_loss, Adam{});
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_ERR_HIP;
 }
 
@@ -538,7 +705,8 @@ lbm_status lbm_mlp_forward(const float* d_params, const lbm_mlp_norm* norm, cons
   if (n == 0) return LBM_OK;
   hipStream_t st = (hipStream_t)hip_stream;
   const Norm nm = to_norm(norm);
-  const int nb = (n + TS - 1) / TS;
+  // each workgroup fetches 130 KB of weights: at most 512 of them walk the tiles
+  const int tiles = (n + TS - 1) / TS, nb = tiles < 512 ? tiles : 512;
   if (flags & LBM_MLP_BF16)
     hipLaunchKernelGGL(k_mlp_forward<1>, dim3(nb), dim3(NT), 0, st, d_params, nm, d_x, n, d_y);
   else
@@ -550,12 +718,9 @@ lbm_status lbm_mlp_grad(const float* d_params, const lbm_mlp_norm* norm, const f
                         const float* d_y, int32_t n_rows, const int32_t* d_idx, int32_t n,
                         float* d_grad, float* d_loss, int32_t flags, void* d_workspace,
                         size_t bytes, void* hip_stream) {
-  lbm_status s = grad_args_ok(d_params, norm, d_x, d_y, n_rows, d_idx, n, d_grad, flags);
+  const lbm_status s = grad_ws_ok(d_params, norm, d_x, d_y, n_rows, d_idx, n, d_grad, flags,
+                                  d_workspace, bytes);
   if (s != LBM_OK) return s;
-  size_t need;
-  lbm_mlp_workspace_bytes(n, &need);
-  if (!d_workspace || bytes < need || ((uintptr_t)d_workspace % 256) != 0)
-    return LBM_ERR_WORKSPACE;
   return grad_launch(d_params, norm, d_x, d_y, n_rows, d_idx, n, d_grad, d_loss, flags,
                      (char*)d_workspace, (hipStream_t)hip_stream);
 }
@@ -584,11 +749,9 @@ lbm_status lbm_mlp_adam(float* d_params, float* d_m, float* d_v, const float* d_
   if (!d_params || !d_m || !d_v || !d_grad || t < 1 || !(lr >= 0.0f) || !(beta1 >= 0.0f) ||
       !(beta1 < 1.0f) || !(beta2 >= 0.0f) || !(beta2 < 1.0f) || !(eps > 0.0f))
     return LBM_ERR_INVALID_ARG;
-  const float bc1 = (float)(1.0 - pow((double)beta1, (double)t));
-  const float bc2 = (float)(1.0 - pow((double)beta2, (double)t));
+  const Adam ad = make_adam(d_params, d_m, d_v, t, lr, beta1, beta2, eps);
   hipLaunchKernelGGL(k_mlp_adam, dim3((NPARAM + 255) / 256), dim3(256), 0,
-                     (hipStream_t)hip_stream, d_params, d_m, d_v, d_grad, lr, beta1, beta2, eps,
-                     bc1, bc2);
+                     (hipStream_t)hip_stream, d_grad, ad);
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_ERR_HIP;
 }
 
@@ -598,10 +761,12 @@ lbm_status lbm_mlp_train_step(float* d_params, float* d_m, float* d_v, int64_t t
                               float* d_loss, int32_t flags, void* d_workspace, size_t bytes,
                               void* hip_stream) {
   if (!d_m || !d_v || t < 1 || !(lr >= 0.0f)) return LBM_ERR_INVALID_ARG;
-  lbm_status s = lbm_mlp_grad(d_params, norm, d_x, d_y, n_rows, d_idx, n, d_grad, d_loss, flags,
-                              d_workspace, bytes, hip_stream);
+  lbm_status s = grad_ws_ok(d_params, norm, d_x, d_y, n_rows, d_idx, n, d_grad, flags, d_workspace,
+                            bytes);
   if (s != LBM_OK) return s;
-  return lbm_mlp_adam(d_params, d_m, d_v, d_grad, t, lr, 0.9f, 0.999f, 1e-8f, hip_stream);
+  const Adam ad = make_adam(d_params, d_m, d_v, t, lr, 0.9f, 0.999f, 1e-8f);
+  return grad_launch(d_params, norm, d_x, d_y, n_rows, d_idx, n, d_grad, d_loss, flags,
+                     (char*)d_workspace, (hipStream_t)hip_stream, &ad);
 }
 
 }  // extern "C"

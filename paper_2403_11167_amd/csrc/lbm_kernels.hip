@@ -2147,68 +2147,6 @@ __global__ void k_set_pop(const double* __restrict__ f, S* __restrict__ dst,
 }
 
 // ---- observation (FP64) -------------------------------------------------------
-// Pass 1: rho (Eq. 6a) and, for P, psi (Eq. 11) on every node.
-template <int MODEL, int EOS, class S>
-__global__ void k_obs_rho(const S* __restrict__ src, const KParams<double> kp,
-                          double* __restrict__ rho_w, double* __restrict__ aux_w,
-                          unsigned* __restrict__ flags) {
-  __shared__ unsigned s_flag;
-  if (threadIdx.x == 0) s_flag = 0u;
-  __syncthreads();
-  const int nx = kp.nx, ny = kp.ny;
-  const size_t N = (size_t)nx * ny;
-  unsigned fl = 0;
-  for (size_t n = blockIdx.x * (size_t)blockDim.x + threadIdx.x; n < N;
-       n += (size_t)gridDim.x * blockDim.x) {
-    int x = (int)(n % nx), y = (int)(n / nx);
-    int xm = (x == 0) ? nx - 1 : x - 1, xp = (x == nx - 1) ? 0 : x + 1;
-    const int rw = kp.rowpitch;
-    int r0 = y * rw, rm = wrapi(y - 1, ny) * rw, rp = wrapi(y + 1, ny) * rw;
-    double g[9];
-    pull9(src, rm, r0, rp, colo(xm), colo(x), colo(xp), g);
-    const int sd = kp.walls ? wall_side(y, ny) : 0;
-    if (sd) wall_fill_fe(g, sd, kp);  // kp.g = 0 for the pseudopotential
-    double rho = kp.rho_ref + sum9(g);
-    fl |= domain_flags<MODEL, EOS>(rho, kp);
-    rho_w[n] = rho;
-    if (MODEL == MODEL_P) aux_w[n] = psi_of<EOS>(rho, kp, fl);
-  }
-  commit_flags(fl, flags, &s_flag);
-}
-
-template <class C>
-__device__ __forceinline__ void gather_global(const C* __restrict__ a, int nx,
-                                              int ny, int walls, int x, int y, C v[9]) {
-  int xm = (x == 0) ? nx - 1 : x - 1, xp = (x == nx - 1) ? 0 : x + 1;
-  int ym = (walls && y == 0) ? 1 : wrapi(y - 1, ny);        // mirrored past a wall
-  int yp = (walls && y == ny - 1) ? ny - 2 : wrapi(y + 1, ny);
-  int r0 = y * nx, rm = ym * nx, rp = yp * nx;
-  v[0] = a[r0 + x];
-  v[1] = a[r0 + xp];
-  v[2] = a[rp + x];
-  v[3] = a[r0 + xm];
-  v[4] = a[rm + x];
-  v[5] = a[rp + xp];
-  v[6] = a[rp + xm];
-  v[7] = a[rm + xm];
-  v[8] = a[rm + xp];
-}
-
-// Pass 2 (FE): mu = mu_b(rho) - kappa lap(rho).
-template <int EOS>
-__global__ void k_obs_mu(const KParams<double> kp, const double* __restrict__ rho_w,
-                         double* __restrict__ aux_w) {
-  const int nx = kp.nx, ny = kp.ny;
-  const size_t N = (size_t)nx * ny;
-  for (size_t n = blockIdx.x * (size_t)blockDim.x + threadIdx.x; n < N;
-       n += (size_t)gridDim.x * blockDim.x) {
-    int x = (int)(n % nx), y = (int)(n / nx);
-    double v[9];
-    gather_global(rho_w, nx, ny, kp.walls, x, y, v);
-    aux_w[n] = eos_mu<EOS>(v[0], kp) - kp.kappa * lap9(v);
-  }
-}
-
 struct ObsPartial {
   double sum_hi, sum_lo, max_u, rho_min, rho_max, du_max, pad0, pad1;
 };
@@ -2269,103 +2207,159 @@ __device__ __forceinline__ ObsPartial obs_block_reduce(ObsPartial a) {
   return a;
 }
 
-// Pass 3: force, velocity (Eq. 6b), exports, per-block partial reductions.
-template <int MODEL, class S, int NT>
-__global__ __launch_bounds__(NT) void k_obs_u(
-    const S* __restrict__ src, const KParams<double> kp,
-    const double* __restrict__ rho_w, const double* __restrict__ aux_w,
-    double* __restrict__ out_rho, double* __restrict__ out_ux,
-    double* __restrict__ out_uy, double* __restrict__ uxp,
-    double* __restrict__ uyp, int have_prev, ObsPartial* __restrict__ part) {
+// Observation in one pass over the populations: a workgroup takes tiles of
+// kObsTX x kObsTY nodes with their stencil halo (1 node for the pseudopotential,
+// 2 for the free energy) into LDS: density (Eq. 6a) and psi (Eq. 11) or mu
+// (Sec. 2.2), then force, velocity (Eq. 6b), exports and partial reductions.
+// Bound by HBM on a large lattice (72 B of FP64 populations and 40 B of fields
+// per node; in three passes the populations were read twice and the fields in
+// between written and read), by launches on a small one (each pass was 4 - 6
+// us).  Past a wall rho, psi and mu are those of the mirrored row.  (Combining
+// the partials in the last workgroup to finish saves k_obs_final's launch but
+// costs every workgroup a release fence, which writes the whole L2 back:
+// 1000 x 777 took 306 us instead of 86.)
+constexpr int kObsTX = 64, kObsTY = 8, kObsNT = 512;
+
+template <int MODEL, int EOS, class S>
+__global__ __launch_bounds__(kObsNT) void k_obs_all(
+    const S* __restrict__ src, const KParams<double> kp, double* __restrict__ out_rho,
+    double* __restrict__ out_ux, double* __restrict__ out_uy, double* __restrict__ uxp,
+    double* __restrict__ uyp, int have_prev, ObsPartial* __restrict__ part,
+    unsigned* __restrict__ flags, int cx, int cy, double* __restrict__ res) {
+  constexpr int HL = MODEL == MODEL_P ? 1 : 2;
+  constexpr int W = kObsTX + 2 * HL, R = kObsTY + 2 * HL, WM = kObsTX + 2, RM = kObsTY + 2;
+  constexpr int NPT = (W * R + kObsNT - 1) / kObsNT;
+  __shared__ double Aq[R][W];  // rho (FE) or psi (P), the tile and HL nodes a side
+  __shared__ double Mu[MODEL == MODEL_FE ? RM : 1][WM];  // the tile and 1 node a side
+  __shared__ unsigned s_flag;
+  if (threadIdx.x == 0) s_flag = 0u;
   const int nx = kp.nx, ny = kp.ny;
-  const size_t N = (size_t)nx * ny;
+  const bool walls = kp.walls != 0;
+  const int ntx = (nx + kObsTX - 1) / kObsTX, ntiles = ntx * ((ny + kObsTY - 1) / kObsTY);
+  const int xi = wrapi(cx, nx), yi = wrapi(cy, ny);                    // probes
+  const int xo = wrapi(cx + nx / 2, nx), yo = wrapi(cy + ny / 2, ny);
+  unsigned fl = 0;
   double s_hi = 0.0, s_lo = 0.0, mu = 0.0, rmin = INFINITY, rmax = -INFINITY, du = 0.0;
-  for (size_t n = blockIdx.x * (size_t)blockDim.x + threadIdx.x; n < N;
-       n += (size_t)gridDim.x * blockDim.x) {
-    int x = (int)(n % nx), y = (int)(n / nx);
-    int xm = (x == 0) ? nx - 1 : x - 1, xp = (x == nx - 1) ? 0 : x + 1;
-    const int rw = kp.rowpitch;
-    int r0 = y * rw, rm = wrapi(y - 1, ny) * rw, rp = wrapi(y + 1, ny) * rw;
-    double g[9];
-    pull9(src, rm, r0, rp, colo(xm), colo(x), colo(xp), g);
-    const int sd = kp.walls ? wall_side(y, ny) : 0;
-    if (sd) wall_fill_fe(g, sd, kp);
-    double rho = rho_w[n];
-    double Fx, Fy;
-    if (MODEL == MODEL_P) {
-      double v[9], sx, sy;
-      gather_global(aux_w, nx, ny, kp.walls, x, y, v);
-      grad_sum(v, sx, sy);
-      Fx = v[0] * sx + kp.fx;
-      Fy = v[0] * sy + kp.fy;
-    } else {
-      double v[9], sx, sy;
-      gather_global(aux_w, nx, ny, kp.walls, x, y, v);
-      grad_sum(v, sx, sy);
-      Fx = -rho * sx + kp.fx;  // F = -rho grad(mu), Eq. 24 gradient
-      Fy = -rho * sy + kp.fy;
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int x0 = (tile % ntx) * kObsTX, y0 = (tile / ntx) * kObsTY;
+    const int w = min(kObsTX, nx - x0), h = min(kObsTY, ny - y0);
+    const int ww = w + 2 * HL, n1 = ww * (h + 2 * HL);
+    double g[NPT][9], rho[NPT];
+    __syncthreads();  // the previous tile's LDS is read
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      const int n = threadIdx.x + q * kObsNT;
+      if (n >= n1) continue;
+      const int r = n / ww, c = n - r * ww;
+      int y = y0 - HL + r;
+      if (walls) y = seen_row(y, ny);
+      y = wrapi(y, ny);
+      const int x = wrapi(x0 - HL + c, nx);
+      const int xm = (x == 0) ? nx - 1 : x - 1, xp = (x == nx - 1) ? 0 : x + 1;
+      const int ym = (y == 0) ? ny - 1 : y - 1, yp = (y == ny - 1) ? 0 : y + 1;
+      pull9(src, ym * kp.rowpitch, y * kp.rowpitch, yp * kp.rowpitch, colo(xm), colo(x), colo(xp),
+            g[q]);
+      const int sd = walls ? wall_side(y, ny) : 0;
+      if (sd) wall_fill_fe(g[q], sd, kp);  // kp.g = 0 for the pseudopotential
+      rho[q] = kp.rho_ref + sum9(g[q]);
+      fl |= domain_flags<MODEL, EOS>(rho[q], kp);
+      if constexpr (MODEL == MODEL_P) Aq[r][c] = psi_of<EOS>(rho[q], kp, fl);
+      else Aq[r][c] = rho[q];
     }
-    if (kp.ax != 0.0) Fx += drive_fx(kp, x, rho);
-    if (sd) Fy = kp.fy;  // zero normal interaction force on a wall row
-    if (kp.g != 0.0) Fy -= (rho - kp.grho0) * kp.g;  // buoyancy (FE gravity)
-    if (sd) wall_fx(g, sd, Fx);
-    double jx = (g[1] - g[3]) + ((g[5] - g[7]) - (g[6] - g[8]));
-    double jy = (g[2] - g[4]) + ((g[5] - g[7]) + (g[6] - g[8]));
-    double ux = (jx + 0.5 * Fx) / rho, uy = (jy + 0.5 * Fy) / rho;
-    if (out_rho) out_rho[n] = rho;
-    if (out_ux) out_ux[n] = ux;
-    if (out_uy) out_uy[n] = uy;
-    if (have_prev) {
-      double dx = ux - uxp[n], dy = uy - uyp[n];
-      du = fmax(du, sqrt(dx * dx + dy * dy));
+    __syncthreads();
+    if constexpr (MODEL == MODEL_FE) {
+      const int wm = w + 2, n2 = wm * (h + 2);
+      for (int n = threadIdx.x; n < n2; n += kObsNT) {
+        const int r = n / wm, c = n - r * wm;
+        int y = y0 - 1 + r;
+        if (walls) y = seen_row(y, ny);  // past a wall: mu of the mirrored row itself
+        const int ra = y - (y0 - HL);
+        double v[9];
+        gather(Aq[ra - 1], Aq[ra], Aq[ra + 1], c + 1, v);
+        Mu[r][c] = eos_mu<EOS>(v[0], kp) - kp.kappa * lap9(v);
+      }
+      __syncthreads();
     }
-    uxp[n] = ux;
-    uyp[n] = uy;
-    // Neumaier accumulation of the mass
-    double s, e;
-    two_sum(s_hi, rho, s, e);
-    s_hi = s;
-    s_lo += e;
-    mu = fmax(mu, sqrt(ux * ux + uy * uy));
-    // rho_min stays NaN once a non-finite density was seen (fmin would drop it)
-    rmin = (rmin != rmin || !__builtin_isfinite(rho)) ? NAN : fmin(rmin, rho);
-    rmax = fmax(rmax, rho);
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      const int n = threadIdx.x + q * kObsNT;
+      const int r = n / ww, c = n - r * ww;
+      if (n >= n1 || r < HL || r >= HL + h || c < HL || c >= HL + w) continue;
+      const int x = x0 + c - HL, y = y0 + r - HL;
+      double v[9], sx, sy, Fx, Fy;
+      if constexpr (MODEL == MODEL_P) {
+        gather(Aq[r - 1], Aq[r], Aq[r + 1], c, v);
+        grad_sum(v, sx, sy);
+        Fx = v[0] * sx + kp.fx;
+        Fy = v[0] * sy + kp.fy;
+      } else {
+        gather(Mu[r - 2], Mu[r - 1], Mu[r], c - 1, v);
+        grad_sum(v, sx, sy);
+        Fx = -rho[q] * sx + kp.fx;  // F = -rho grad(mu), Eq. 24 gradient
+        Fy = -rho[q] * sy + kp.fy;
+      }
+      const int sd = walls ? wall_side(y, ny) : 0;
+      if (kp.ax != 0.0) Fx += drive_fx(kp, x, rho[q]);
+      if (sd) Fy = kp.fy;  // zero normal interaction force on a wall row
+      if (kp.g != 0.0) Fy -= (rho[q] - kp.grho0) * kp.g;  // buoyancy (FE gravity)
+      if (sd) wall_fx(g[q], sd, Fx);
+      const double jx = (g[q][1] - g[q][3]) + ((g[q][5] - g[q][7]) - (g[q][6] - g[q][8]));
+      const double jy = (g[q][2] - g[q][4]) + ((g[q][5] - g[q][7]) + (g[q][6] - g[q][8]));
+      const double ux = (jx + 0.5 * Fx) / rho[q], uy = (jy + 0.5 * Fy) / rho[q];
+      const size_t o = (size_t)y * nx + x;
+      if (out_rho) out_rho[o] = rho[q];
+      if (out_ux) out_ux[o] = ux;
+      if (out_uy) out_uy[o] = uy;
+      if (have_prev) {
+        double dx = ux - uxp[o], dy = uy - uyp[o];
+        du = fmax(du, sqrt(dx * dx + dy * dy));
+      }
+      uxp[o] = ux;
+      uyp[o] = uy;
+      if (x == xi && y == yi) res[4] = rho[q];
+      if (x == xo && y == yo) res[5] = rho[q];
+      // Neumaier accumulation of the mass
+      double s, e;
+      two_sum(s_hi, rho[q], s, e);
+      s_hi = s;
+      s_lo += e;
+      mu = fmax(mu, sqrt(ux * ux + uy * uy));
+      // rho_min stays NaN once a non-finite density was seen (fmin would drop it)
+      rmin = (rmin != rmin || !__builtin_isfinite(rho[q])) ? NAN : fmin(rmin, rho[q]);
+      rmax = fmax(rmax, rho[q]);
+    }
   }
+  commit_flags(fl, flags, &s_flag);
   const ObsPartial blk =
-      obs_block_reduce<NT>(ObsPartial{s_hi, s_lo, mu, rmin, rmax, du, 0.0, 0.0});
+      obs_block_reduce<kObsNT>(ObsPartial{s_hi, s_lo, mu, rmin, rmax, du, 0.0, 0.0});
   if (threadIdx.x == 0) part[blockIdx.x] = blk;
 }
 
-// Pass 4: one workgroup combines the partials in a fixed order and forms the
-// probe observables (Sec. 5.2: pressure jump, equimolar radius).
+// One workgroup combines the partials in a fixed order and forms the probe
+// observables (Sec. 5.2: pressure jump, equimolar radius).
 template <int EOS, int NT>
-__global__ __launch_bounds__(NT) void k_obs_final(
-    const ObsPartial* __restrict__ part, int nparts, const KParams<double> kp,
-    const double* __restrict__ rho_w, int cx, int cy, double* __restrict__ res) {
+__global__ __launch_bounds__(NT) void k_obs_final(const ObsPartial* __restrict__ part, int nparts,
+                                                  const KParams<double> kp,
+                                                  const unsigned* __restrict__ flags,
+                                                  double* __restrict__ res) {
   ObsPartial acc{0.0, 0.0, 0.0, INFINITY, -INFINITY, 0.0, 0.0, 0.0};
   for (int i = threadIdx.x; i < nparts; i += NT) acc = obs_combine(acc, part[i]);
-  const ObsPartial a = obs_block_reduce<NT>(acc);
+  const ObsPartial t = obs_block_reduce<NT>(acc);
   if (threadIdx.x == 0) {
-    const int nx = kp.nx, ny = kp.ny;
-    double mass = a.sum_hi + a.sum_lo;
-    int xi = wrapi(cx, nx), yi = wrapi(cy, ny);
-    int xo = wrapi(cx + nx / 2, nx), yo = wrapi(cy + ny / 2, ny);
-    double rin = rho_w[(size_t)yi * nx + xi];
-    double rout = rho_w[(size_t)yo * nx + xo];
-    double dp = eos_p<EOS>(rin, kp) - eos_p<EOS>(rout, kp);
-    double excess = mass - (double)nx * (double)ny * rout;
-    double denom = 3.14159265358979323846 * (rin - rout);
-    double q = (denom != 0.0) ? excess / denom : NAN;
-    double req = (q > 0.0) ? sqrt(q) : NAN;
+    const double mass = t.sum_hi + t.sum_lo;
+    const double rin = res[4], rout = res[5];  // the probes, by k_obs_all
+    const double dp = eos_p<EOS>(rin, kp) - eos_p<EOS>(rout, kp);
+    const double excess = mass - (double)kp.nx * (double)kp.ny * rout;
+    const double denom = 3.14159265358979323846 * (rin - rout);
+    const double q = (denom != 0.0) ? excess / denom : NAN;
     res[0] = mass;
-    res[1] = a.max_u;
-    res[2] = a.rho_min;
-    res[3] = a.rho_max;
-    res[4] = rin;
-    res[5] = rout;
+    res[1] = t.max_u;
+    res[2] = t.rho_min;
+    res[3] = t.rho_max;
     res[6] = dp;
-    res[7] = req;
-    res[8] = a.du_max;
+    res[7] = (q > 0.0) ? sqrt(q) : NAN;
+    res[8] = t.du_max;
+    res[9] = (double)*flags;  // rides along (exact in a double)
   }
 }
 
@@ -2378,7 +2372,6 @@ using namespace lbmk;
 
 namespace {
 
-constexpr int kObsThreads = 256;
 constexpr int kGraphSteps = 16;  // steps per graph run of lbm_step (even)
 constexpr int kObsBlocksMax = 2048;
 constexpr size_t kAlign = 256;
@@ -2389,7 +2382,7 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 size_t row_pitch(int nx) { return (size_t)576 * (size_t)((nx + 63) / 64); }
 
 struct Layout {
-  size_t pop_bytes, fA, fB, rho_w, aux_w, uxp, uyp, uax, uay, part, flags, result, total;
+  size_t pop_bytes, fA, fB, uxp, uyp, uax, uay, part, flags, result, total;
   int obs_blocks;
 };
 
@@ -2401,15 +2394,17 @@ Layout make_layout(const lbm_params* p) {
   size_t off = 0;
   L.fA = off; off += L.pop_bytes;
   L.fB = off; off += L.pop_bytes;
-  L.rho_w = off; off += align_up(N * 8);
-  L.aux_w = off; off += align_up(N * 8);
   L.uxp = off; off += align_up(N * 8);
   L.uyp = off; off += align_up(N * 8);
+  // two fields of doubles not in use (callers know the size of a workspace as
+  // the populations and four fields)
+  off += 2 * align_up(N * 8);
   // FE with A != 0: the velocity field of the current step
   const size_t ua = (p->model == LBM_MODEL_FE && p->A != 0.0) ? align_up(N * 8) : 0;
   L.uax = off; off += ua;
   L.uay = off; off += ua;
-  L.obs_blocks = (int)std::min<size_t>((N + kObsThreads - 1) / kObsThreads, kObsBlocksMax);
+  const size_t obs_tiles = (size_t)((p->nx + kObsTX - 1) / kObsTX) * ((p->ny + kObsTY - 1) / kObsTY);
+  L.obs_blocks = (int)std::min<size_t>(obs_tiles, kObsBlocksMax);
   L.part = off; off += align_up((size_t)L.obs_blocks * sizeof(ObsPartial));
   L.flags = off; off += kAlign;
   L.result = off; off += align_up(16 * sizeof(double));
@@ -3137,25 +3132,14 @@ void launch_init(lbm_ctx* c, const double* rho0) {
 template <int MODEL, int EOS, class S>
 void launch_observe(lbm_ctx* c, int cx, int cy, double* d_rho, double* d_ux, double* d_uy) {
   const S* src = (const S*)(c->ws + (c->cur ? c->L.fB : c->L.fA));
-  double* rho_w = (double*)(c->ws + c->L.rho_w);
-  double* aux_w = (double*)(c->ws + c->L.aux_w);
-  double* uxp = (double*)(c->ws + c->L.uxp);
-  double* uyp = (double*)(c->ws + c->L.uyp);
-  ObsPartial* part = (ObsPartial*)(c->ws + c->L.part);
   unsigned* flags = (unsigned*)(c->ws + c->L.flags);
-  double* res = (double*)(c->ws + c->L.result);
-  size_t N = (size_t)c->p.nx * c->p.ny;
-  hipLaunchKernelGGL((k_obs_rho<MODEL, EOS, S>), dim3(grid1d(N)), dim3(256), 0, c->stream,
-                     src, c->kd, rho_w, aux_w, flags);
-  if (MODEL == MODEL_FE)
-    hipLaunchKernelGGL((k_obs_mu<EOS>), dim3(grid1d(N)), dim3(256), 0, c->stream, c->kd,
-                       (const double*)rho_w, aux_w);
-  hipLaunchKernelGGL((k_obs_u<MODEL, S, kObsThreads>), dim3(c->L.obs_blocks),
-                     dim3(kObsThreads), 0, c->stream, src, c->kd, (const double*)rho_w,
-                     (const double*)aux_w, d_rho, d_ux, d_uy, uxp, uyp, c->have_prev, part);
-  hipLaunchKernelGGL((k_obs_final<EOS, kObsThreads>), dim3(1), dim3(kObsThreads), 0,
-                     c->stream, (const ObsPartial*)part, c->L.obs_blocks, c->kd,
-                     (const double*)rho_w, cx, cy, res);
+  hipLaunchKernelGGL((k_obs_all<MODEL, EOS, S>), dim3(c->L.obs_blocks), dim3(kObsNT), 0, c->stream,
+                     src, c->kd, d_rho, d_ux, d_uy, (double*)(c->ws + c->L.uxp),
+                     (double*)(c->ws + c->L.uyp), c->have_prev, (ObsPartial*)(c->ws + c->L.part),
+                     flags, cx, cy, (double*)(c->ws + c->L.result));
+  hipLaunchKernelGGL((k_obs_final<EOS, 256>), dim3(1), dim3(256), 0, c->stream,
+                     (const ObsPartial*)(c->ws + c->L.part), c->L.obs_blocks, c->kd,
+                     (const unsigned*)flags, (double*)(c->ws + c->L.result));
 }
 
 template <int MODEL, int EOS>
@@ -3265,11 +3249,8 @@ lbm_status observe_impl(lbm_ctx* c, int32_t cx, int32_t cy, lbm_obs* out,
     else observe_dispatch_prec<MODEL_FE, EOS_VDW>(c, cx, cy, d_rho, d_ux, d_uy);
   }
   if (hipGetLastError() != hipSuccess) return LBM_ERR_HIP;
-  double res[9];
-  unsigned flags = 0;
+  double res[10];
   if (hipMemcpyAsync(res, c->ws + c->L.result, sizeof(res), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
-    return LBM_ERR_HIP;
-  if (hipMemcpyAsync(&flags, c->ws + c->L.flags, sizeof(flags), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
     return LBM_ERR_HIP;
   if (hipStreamSynchronize(c->stream) != hipSuccess) return LBM_ERR_HIP;
   out->step = c->step;
@@ -3282,7 +3263,7 @@ lbm_status observe_impl(lbm_ctx* c, int32_t cx, int32_t cy, lbm_obs* out,
   out->dp = res[6];
   out->r_equimolar = res[7];
   out->du_max = c->have_prev ? res[8] : INFINITY;
-  out->flags = flags;
+  out->flags = (uint32_t)res[9];
   out->reserved = 0;
   c->have_prev = 1;
   return LBM_OK;

@@ -167,9 +167,11 @@ typedef struct {
                                    the intermediate populations stay on
                                    chip; results are bit-identical to two
                                    single steps                            */
-#define LBM_KF_STRIP128 32u     /* the free-energy two-step kernel on
-                                   128-column strips (the default)         */
-#define LBM_KF_STRIP192 64u     /* ... on 192-column strips                */
+#define LBM_KF_STRIP128 32u     /* the free-energy two-step kernel in
+                                   workgroups of 128 lanes on strips of up
+                                   to 112 columns (neither flag: 256 lanes,
+                                   240 columns)                            */
+#define LBM_KF_STRIP192 64u     /* ... of 192 lanes, 176 columns           */
 #define LBM_KF_PATCH 128u       /* patches wherever the default launch shape
                                    would take them; elsewhere as the other
                                    fields say                              */

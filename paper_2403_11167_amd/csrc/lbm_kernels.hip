@@ -95,6 +95,25 @@ template <class C>
 __device__ __forceinline__ C d_sqrt(C v) {
   if constexpr (sizeof(C) == 4) return sqrtf(v); else return sqrt(v);
 }
+
+// The same root with fewer instructions in FP32: the hardware estimate y of
+// 1/sqrt(v) and one residual step, s = v y, s + (v - s s) y / 2, give the
+// correctly rounded root of every float in [2^-60, 2^60] (compared with sqrtf
+// for each of those floats on gfx950: no difference); sqrtf scales against
+// denormals and searches the neighbouring floats, and serves a wavefront
+// with a value outside.  The two-step kernel alone takes it: the register
+// caps of the others have no room for both.
+template <class C>
+__device__ __forceinline__ C d_sqrt_sweep(C v) {
+  if constexpr (sizeof(C) == 4) {
+    if (__builtin_expect(__ballot(!(v >= 0x1p-60f && v <= 0x1p60f)) != 0ull, 0)) return sqrtf(v);
+    const float y = __builtin_amdgcn_rsqf(v);
+    const float s = v * y;
+    return fmaf(fmaf(-s, s, v), 0.5f * y, s);
+  } else {
+    return sqrt(v);
+  }
+}
 // Logarithms of the chemical potential: the reduced-range atanh series of
 // lbm_math.h (a few ulps, a third of the library functions' instructions).
 template <class C>
@@ -210,8 +229,13 @@ __device__ __forceinline__ unsigned domain_flags(C rho, const KParams<C>& kp) {
 // Yuan-Schaefer potential, Eq. 11 with G = -1: psi^2 = 2 (rho c_s^2 - p).
 // A negative psi^2 is clamped to zero and flagged.
 template <int EOS, class C>
+__device__ __forceinline__ C psi_sq(C rho, const KParams<C>& kp) {
+  return C(2) * (rho * C(1.0 / 3.0) - eos_p<EOS>(rho, kp));
+}
+
+template <int EOS, class C>
 __device__ __forceinline__ C psi_of(C rho, const KParams<C>& kp, unsigned& fl) {
-  C arg = C(2) * (rho * C(1.0 / 3.0) - eos_p<EOS>(rho, kp));
+  C arg = psi_sq<EOS>(rho, kp);
   if (arg < C(0)) {
     fl |= LBM_FLAG_PSI_CLAMP;
     arg = C(0);
@@ -250,6 +274,38 @@ __device__ __forceinline__ void pull9(const S* __restrict__ src, int rm, int r0,
   g[6] = (C)ld<NT>(&src[rm + cp + 384]);
   g[7] = (C)ld<NT>(&src[rp + cp + 448]);
   g[8] = (C)ld<NT>(&src[rp + cm + 512]);
+}
+
+// The same pull for the row sweeps, whose rows are uniform in the workgroup:
+// the row stays in scalar registers and the lane adds a 32-bit byte offset
+// (of column x-1, x, x+1), so the nine addresses cost no vector arithmetic.
+// The base is that of velocity 4, which keeps every velocity's offset within
+// the load's immediate.
+template <class S>
+__device__ __forceinline__ const S* at_row(const S* __restrict__ src, int row, unsigned b) {
+  return reinterpret_cast<const S*>(reinterpret_cast<const char*>(src + row + 256) + b) - 256;
+}
+
+template <class S, class C, int NT>
+__device__ __forceinline__ void pull9_rows(const S* __restrict__ src, int rm, int r0, int rp,
+                                           unsigned bm, unsigned b0, unsigned bp, C g[9]) {
+  g[0] = (C)ld<NT>(at_row(src, r0, b0));
+  g[1] = (C)ld<NT>(at_row(src, r0, bm) + 64);
+  g[2] = (C)ld<NT>(at_row(src, rm, b0) + 128);
+  g[3] = (C)ld<NT>(at_row(src, r0, bp) + 192);
+  g[4] = (C)ld<NT>(at_row(src, rp, b0) + 256);
+  g[5] = (C)ld<NT>(at_row(src, rm, bm) + 320);
+  g[6] = (C)ld<NT>(at_row(src, rm, bp) + 384);
+  g[7] = (C)ld<NT>(at_row(src, rp, bp) + 448);
+  g[8] = (C)ld<NT>(at_row(src, rp, bm) + 512);
+}
+
+template <int NT, class S, class C>
+__device__ __forceinline__ void store9_row(S* __restrict__ dst, int row, unsigned b0,
+                                           const C g[9]) {
+  S* o = reinterpret_cast<S*>(reinterpret_cast<char*>(dst + row + 256) + b0);
+#pragma unroll
+  for (int i = 0; i < 9; ++i) st<NT>(&o[64 * i - 256], (S)g[i]);
 }
 
 template <class C>
@@ -463,6 +519,56 @@ __device__ __forceinline__ void commit_flags(unsigned fl, unsigned* __restrict__
     if (v && (v & ~__atomic_load_n(flags, __ATOMIC_RELAXED))) atomicOr(flags, v);
   }
 }
+
+// Fixes where a value is formed: without it the compiler sinks the arithmetic
+// of values that are next used an iteration later past the stage that forms
+// them, and holds that stage's temporaries in registers instead.
+template <class C>
+__device__ __forceinline__ void pin(C& v) {
+  asm volatile("" : "+v"(v));
+}
+template <class C>
+__device__ __forceinline__ void pin9(C v[9]) {
+#pragma unroll
+  for (int i = 0; i < 9; ++i) pin(v[i]);
+}
+
+// Flag bits of the two-step row sweeps.  SCALAR: one 64-lane mask per flag in
+// scalar registers, so that a test costs its compare and nothing more; every
+// lane of the wavefront takes part (uniform control) and `lanes` are those
+// whose node counts.  Otherwise one word per lane, for tests under a lane
+// condition, and `lanes` has no effect.
+template <int SCALAR>
+struct SweepFlags {
+  unsigned long long nonfinite = 0, clamp = 0, domain = 0;
+  unsigned fl = 0;
+  __device__ __forceinline__ unsigned bits() const {
+    if constexpr (!SCALAR) return fl;
+    return (nonfinite ? LBM_FLAG_NONFINITE : 0u) | (clamp ? LBM_FLAG_PSI_CLAMP : 0u) |
+           (domain ? LBM_FLAG_EOS_DOMAIN : 0u);
+  }
+  template <int MODEL, int EOS, class C>
+  __device__ __forceinline__ void check(C rho, const KParams<C>& kp, unsigned long long lanes) {
+    if constexpr (!SCALAR) {
+      fl |= domain_flags<MODEL, EOS>(rho, kp);
+    } else {
+      nonfinite |= __ballot(!__builtin_isfinite(rho)) & lanes;
+      const C lim = (EOS == EOS_CS) ? kp.b * rho * C(0.25) : kp.b * rho;
+      domain |= __ballot(!(lim < C(1))) & lanes;
+      if constexpr (MODEL == MODEL_FE) domain |= __ballot(!(rho > C(0))) & lanes;
+    }
+  }
+  template <int EOS, class C>
+  __device__ __forceinline__ C psi(C rho, const KParams<C>& kp, unsigned long long lanes) {
+    if constexpr (!SCALAR) {
+      return psi_of<EOS>(rho, kp, fl);
+    } else {
+      const C arg = psi_sq<EOS>(rho, kp);
+      clamp |= __ballot(arg < C(0)) & lanes;
+      return d_sqrt_sweep(arg < C(0) ? C(0) : arg);
+    }
+  }
+};
 
 __device__ __forceinline__ int wrapi(int v, int n) {
   v %= n;
@@ -867,9 +973,8 @@ __device__ __forceinline__ void tile_p_pipe(const S* __restrict__ src, S* __rest
 
 // Two pseudopotential steps on one tile of a periodic lattice in one pass
 // (temporal blocking): the populations after the first step, g*1, never go
-// to HBM.  The workgroup has BX + 64 threads.  Lanes 0 .. BX-1 own the
-// tile's columns x0 + t for both steps; the last wavefront (the halo
-// wavefront) owns the columns the first step needs around the strip:
+// to HBM.  Lanes t < w <= BX own the tile's w columns x0 + t for both steps;
+// lanes BX + h own the columns the first step needs around the strip:
 // h = 0..3 the four columns x0-2, x0-1, x0+w, x0+w+1, whose g*1 the second
 // step pulls from or needs for its psi halo, and h = 4, 5 the psi-only
 // columns x0-3, x0+w+2.  Per row a of the first step (rows y0-2 ..
@@ -884,20 +989,38 @@ __device__ __forceinline__ void tile_p_pipe(const S* __restrict__ src, S* __rest
 // Every node does the arithmetic of the single-step kernel in the same
 // order, so two steps of this kernel equal two single steps bit for bit.
 // PF = 1 fetches each first-step row one iteration ahead of its use (FP64:
-// the wait for a row leaves the next row's loads in flight; measured
-// 0.33 vs 0.50 ms per step on 4096^2); PF = 0 waits at once (FP32, where the
-// nine more live registers cost a wave of occupancy: 0.159 vs 0.171 ms).
-template <int EOS, class S, class C, int BX, int NT, int PF>
+// the wait for a row leaves the next row's loads in flight; without it the
+// step took half as long again); PF = 0 waits at once (FP32, where the nine
+// more live registers gain nothing: 144 against 142 us per step).
+//
+// What bounds it, and what this layout measured per step on 4096^2 (before:
+// strips of 256 columns with a fifth wavefront for the halo columns, row
+// arithmetic in the vector unit): FP64 337 -> 252 us, 2.4 GB per two steps
+// plus 8 % of halo, so memory; FP32 152 -> 141 us, the vector units, four
+// fifths busy.  The halo columns ride in the last lanes of the strip's own
+// wavefronts: a wavefront of their own issued every instruction for six
+// lanes, a fifth of the work.  Row counter, row offsets and flag masks stay
+// in scalar registers, the nine loads take a scalar row and a 32-bit column
+// offset (618 -> 490 vector instructions a row in FP64), and two rows a turn
+// of the loop take most register moves out.
+// LEAN = 0 (a lattice of its own): every lane takes part in every stage, the
+// straight-line form, 201 registers in FP64 and 109 in FP32.  LEAN = 1
+// (batches, whose 256-column tiles need a wavefront for the halo lanes):
+// stages under lane conditions and one row a turn, 153 and 72 registers, so
+// that two and five of these workgroups of five wavefronts fit a compute
+// unit.
+template <int EOS, class S, class C, int BX, int NT, int PF, int LEAN>
 __device__ __forceinline__ void tile_p2(const S* __restrict__ src, S* __restrict__ dst,
                                         const KParams<C>& kp, unsigned* __restrict__ flags,
-                                        int x0, int y0) {
-  __shared__ C psi1[4][BX + 6];   // columns x0-3 .. x0+w+2
-  __shared__ C xb[6][BX + 4];     // x-moving g*1 of one row, columns x0-2 .. x0+w+1
-  __shared__ C psi2[4][BX + 2];   // columns x0-1 .. x0+w
+                                        int x0, int y0, int sw) {
+  constexpr int SP = LEAN ? 0 : 1;  // the spare element
+  __shared__ C psi1[4][BX + 6 + SP];   // columns x0-3 .. x0+w+2, one for idle lanes
+  __shared__ C xb[6][BX + 4 + SP];     // x-moving g*1 of one row, columns x0-2 .. x0+w+1
+  __shared__ C psi2[4][BX + 2 + SP];   // columns x0-1 .. x0+w
   __shared__ unsigned s_flag;
   if (threadIdx.x == 0) s_flag = 0u;
-  const int nx = kp.nx, ny = kp.ny;
-  const int w = min(BX, nx - x0);
+  const int nx = kp.nx, ny = kp.ny, pitch = kp.rowpitch;
+  const int w = min(sw, nx - x0);
   const int ly = min(kp.LY, ny - y0);
   const int t = threadIdx.x;
   const bool mainl = t < BX;
@@ -913,12 +1036,17 @@ __device__ __forceinline__ void tile_p2(const S* __restrict__ src, S* __restrict
   const int x = wrapi(x0 + (act1 ? off : 0), nx);
   const int xm = (x == 0) ? nx - 1 : x - 1;
   const int xp = (x == nx - 1) ? 0 : x + 1;
-  const int cm = colo(xm), c0 = colo(x), cp = colo(xp);
-  const int j1 = off + 3;  // psi1 index
-  const int jx = off + 2;  // xb index
-  const int j2 = off + 1;  // psi2 index
+  const unsigned cm = colo(xm) * (unsigned)sizeof(S), c0 = colo(x) * (unsigned)sizeof(S),
+                 cp = colo(xp) * (unsigned)sizeof(S);
+  // Every lane takes part in every stage, so that the stages are straight-line
+  // code: a lane without a column there reads the strip's first one and
+  // writes to the spare element past the row.
+  const int w1 = act1 ? off + 3 : BX + 6, j1 = col1 ? off + 3 : 3;  // psi1: write, read
+  const int wx = col1 ? off + 2 : BX + 4, jx = dep2 ? off + 2 : 2;  // xb
+  const int w2 = dep2 ? off + 1 : BX + 2, j2 = col2 ? off + 1 : 1;  // psi2
+  const unsigned long long lanes1 = __ballot(act1), lanes2 = __ballot(dep2);
 
-  unsigned fl = 0;
+  SweepFlags<!LEAN> fl;
   C gc[9], gn[9], g2[9];
   C drho_c = C(0);
   // The second step's pulled populations at the start of iteration a: P of
@@ -929,22 +1057,35 @@ __device__ __forceinline__ void tile_p2(const S* __restrict__ src, S* __restrict
 #pragma unroll
   for (int i = 0; i < 9; ++i) P[i] = Q[i] = C(0);
 
-  auto rowoff = [&](int y) { return wrapi(y, ny) * kp.rowpitch; };
-  // The pulls are unconditional (a lane without a column reads a valid one
-  // and discards it) and one row ahead of their use, so that the wait for a
-  // row leaves the next row's loads in flight (see tile_p_pipe).
-  // (PF = 0: only lanes with a column load)
-  auto pull = [&](int y, C g[9]) {
-    const int r0 = rowoff(y), rm = rowoff(y - 1), rp = rowoff(y + 1);
-    if (PF != 0 || act1) pull9<S, C, NT>(src, rm, r0, rp, cm, c0, cp, g);
+  // offsets of the rows around the next one to pull (uniform, so scalar)
+  const int rend = ny * pitch;
+  auto row_after = [&](int o) { return o + pitch == rend ? 0 : o + pitch; };
+  int om = wrapi(y0 - 4, ny) * pitch, o0 = row_after(om), op = row_after(o0);
+  auto stage_end = [&]() {
+    if constexpr (!LEAN) __builtin_amdgcn_sched_barrier(0);
   };
-  auto psi_row = [&](const C g[9], int slot) {
+  auto stage_sync = [&]() {
+    stage_end();
+    __syncthreads();
+    stage_end();
+  };
+  auto pull_next = [&](C g[9]) {
+    if (PF != 0 || !LEAN || act1) pull9_rows<S, C, NT>(src, om, o0, op, cm, c0, cp, g);
+    om = o0;
+    o0 = op;
+    op = row_after(op);
+  };
+  auto psi_row = [&](C g[9], int slot) {
     C dr = C(0);
-    if (act1) {
+    if (!LEAN || act1) {
       dr = sum9(g);
-      C rho = kp.rho_ref + dr;
-      fl |= domain_flags<MODEL_P, EOS>(rho, kp);
-      psi1[slot & 3][j1] = psi_of<EOS>(rho, kp, fl);
+      if constexpr (!LEAN) {
+        pin(dr);
+        pin9(g);
+      }
+      const C rho = kp.rho_ref + dr;
+      fl.template check<MODEL_P, EOS>(rho, kp, lanes1);
+      psi1[slot & 3][w1] = fl.template psi<EOS>(rho, kp, lanes1);
     }
     return dr;
   };
@@ -953,20 +1094,22 @@ __device__ __forceinline__ void tile_p2(const S* __restrict__ src, S* __restrict
   // psi1 slot of row r: (r - y0 + 3) & 3; psi2 slot of row r: (r - y0 + 1) & 3
   {
     C tmp[9];
-    pull(y0 - 3, tmp);
+    pull_next(tmp);
     psi_row(tmp, 0);
-    pull(y0 - 2, gc);
+    pull_next(gc);
     drho_c = psi_row(gc, 1);
-    if constexpr (PF != 0) pull(y0 - 1, gn);
+    if constexpr (PF != 0) pull_next(gn);
   }
-  for (int k = 0; k < ly + 4; ++k) {
+  int k = 0;
+  const int nrow = ly + 4;
+  auto do_row = [&]() {
     // first-step row a = y0 - 2 + k; with PF, row a + 2 is fetched here for
     // the next iteration and row a + 1 was fetched by the previous one
-    if constexpr (PF != 0) pull(y0 + k, g2);
-    else pull(y0 - 1 + k, gn);
+    if constexpr (PF != 0) pull_next(g2);
+    else pull_next(gn);
     const C drho_n = psi_row(gn, k + 2);
-    __syncthreads();
-    if (col1) {
+    stage_sync();
+    if (!LEAN || col1) {
       C v[9];
       gather(psi1[k & 3], psi1[(k + 1) & 3], psi1[(k + 2) & 3], j1, v);
       C sx, sy;
@@ -982,19 +1125,22 @@ __device__ __forceinline__ void tile_p2(const S* __restrict__ src, S* __restrict
       // the single-step kernel stores the first step's output and loads it
       // back: round to the storage type the same way
 #pragma unroll
-      for (int i = 0; i < 9; ++i) gc[i] = (C)(S)gc[i];
-      xb[0][jx] = gc[1];
-      xb[1][jx] = gc[5];
-      xb[2][jx] = gc[8];
-      xb[3][jx] = gc[3];
-      xb[4][jx] = gc[6];
-      xb[5][jx] = gc[7];
+      for (int i = 0; i < 9; ++i) {
+        gc[i] = (C)(S)gc[i];
+        if constexpr (!LEAN) pin(gc[i]);
+      }
+      xb[0][wx] = gc[1];
+      xb[1][wx] = gc[5];
+      xb[2][wx] = gc[8];
+      xb[3][wx] = gc[3];
+      xb[4][wx] = gc[6];
+      xb[5][wx] = gc[7];
     }
-    __syncthreads();
+    stage_sync();
     // deposit row a: +x movers arrive from the column on the left, -x
     // movers from the one on the right
     C l1 = C(0), l5 = C(0), r3 = C(0), r6 = C(0), dq = C(0);
-    if (dep2) {
+    if (!LEAN || dep2) {
       l1 = xb[0][jx - 1];
       l5 = xb[1][jx - 1];
       r3 = xb[3][jx + 1];
@@ -1003,14 +1149,19 @@ __device__ __forceinline__ void tile_p2(const S* __restrict__ src, S* __restrict
       Q[7] = xb[5][jx + 1];   // f_7(x, a-1) = g*1_7(x+1, a)
       Q[8] = xb[2][jx - 1];   // f_8(x, a-1) = g*1_8(x-1, a)
       dq = sum9(Q);
-      if (k >= 2) {  // row a-1 >= y0-1: psi2 of a complete row
-        C rho = kp.rho_ref + dq;
-        fl |= domain_flags<MODEL_P, EOS>(rho, kp);
-        psi2[(k - 2) & 3][j2] = psi_of<EOS>(rho, kp, fl);
+      if constexpr (!LEAN) {
+        pin(dq);
+        pin9(Q);
+      }
+      if (!LEAN || k >= 2) {  // row a-1: complete, and its psi2 valid, from y0-1 on
+        const unsigned long long lanes = k >= 2 ? lanes2 : 0ull;
+        const C rho = kp.rho_ref + dq;
+        fl.template check<MODEL_P, EOS>(rho, kp, lanes);
+        psi2[(k - 2) & 3][w2] = fl.template psi<EOS>(rho, kp, lanes);
       }
     }
-    __syncthreads();
-    if (k >= 4 && col2) {
+    stage_sync();
+    if (k >= 4 && (!LEAN || col2)) {
       // second-step collision of row b = a-2 (psi2 rows b-1, b, b+1)
       const int b = y0 - 4 + k;
       C v[9];
@@ -1025,9 +1176,7 @@ __device__ __forceinline__ void tile_p2(const S* __restrict__ src, S* __restrict
       C rho = kp.rho_ref + drho_p;
       C ux, uy;
       collide<MODEL_P>(P, drho_p, rho, Fx, Fy, K, qs, qd, qxy, kp, ux, uy);
-      const int o = b * kp.rowpitch + c0;
-#pragma unroll
-      for (int i = 0; i < 9; ++i) st<NT>(&dst[o + 64 * i], (S)P[i]);
+      if (col2) store9_row<NT>(dst, b * pitch, c0, P);
     }
     // shift the second step's rows: a-1 -> P, a -> Q, a+1 -> R
 #pragma unroll
@@ -1048,15 +1197,25 @@ __device__ __forceinline__ void tile_p2(const S* __restrict__ src, S* __restrict
       if constexpr (PF != 0) gn[i] = g2[i];
     }
     drho_c = drho_n;
+    // k stays in a scalar register: left to itself the compiler moves the
+    // increment into the arms of the divergent branch above, and the row
+    // arithmetic into the vector unit with it
+    k = __builtin_amdgcn_readfirstlane(k + 1);
+  };
+  while (k < nrow) {
+    do_row();
+    if constexpr (!LEAN) {
+      if (k == nrow) break;
+      do_row();
+    }
   }
-  commit_flags(fl, flags, &s_flag);
+  commit_flags(fl.bits(), flags, &s_flag);
 }
 
 // Two free-energy steps on one tile of a periodic lattice in one pass
 // (temporal blocking): the populations after the first step, g*1, never go
-// to HBM.  The workgroup has BX + 64 threads.  Lanes 0 .. BX-1 own the
-// tile's columns x0 + t for both steps; the last wavefront (the halo
-// wavefront) owns the first step's columns around the strip.  The second
+// to HBM.  Lanes t < w <= BX own the tile's w columns x0 + t for both steps;
+// lanes BX + h own the first step's columns around the strip.  The second
 // step's density is needed two columns beyond the strip (its chemical
 // potential one column beyond), so the first step collides three halo
 // columns each side, needs the chemical potential on four and the density
@@ -1073,9 +1232,8 @@ __device__ __forceinline__ void tile_p2(const S* __restrict__ src, S* __restrict
 //                   density goes into the rho2 ring);
 //   phase 1: B(r-1) chemical potential of row r-1 into the mu1 ring;
 //            E(r-5) chemical potential of the second step, row r-5;
-//   phase 2: C(r-2) pull row r-2 again (its populations were not kept),
-//                   collide it (first step), the x-moving populations into
-//                   LDS for the neighbours' deposits;
+//   phase 2: C(r-2) collide row r-2 (first step), the x-moving populations
+//                   into LDS for the neighbours' deposits;
 //            F(r-6) collide row r-6 (second step) and store it.
 // Each stage reads only what earlier phases wrote, and four-row rings cover
 // the rows that a phase reads while another writes.  Between the deposit
@@ -1085,31 +1243,42 @@ __device__ __forceinline__ void tile_p2(const S* __restrict__ src, S* __restrict
 // output is rounded to the storage type, so two steps of this kernel equal
 // two single steps bit for bit.
 // The first step's row r-2 reaches the collision in one of two ways:
-//   HOLD = 0 (FP64, whose registers are spent): pulled a second time, two
-//            iterations after A pulled it; that pull is issued at the start
+//   HOLD = 0 (FP64 with LEAN, whose registers are spent): pulled a second
+//            time, two iterations after A pulled it; that pull is issued at the start
 //            of phase 1 and A's pull of the next row at the end of phase 2,
 //            after the collisions, so that each is in flight through a
 //            phase of work without adding to the registers the collisions
 //            need;
-//   HOLD = 1 (FP32): A's rows are kept in registers for two iterations, and
-//            the pull of row r+1 is issued in phase 1 for the next
-//            iteration's A, so that it stays in flight through phase 2; 27
-//            more registers per lane.
+//   HOLD = 1 (FP32, and FP64 without LEAN): A's rows are kept in registers
+//            for two iterations, and the pull of row r+1 is issued in phase 1
+//            for the next iteration's A, so that it stays in flight through
+//            phase 2; 27 more registers per lane (FP32).
 // Early pulls are unconditional (a lane without a column reads a valid one),
 // so that a wait for one leaves the later ones in flight (see tile_p_pipe).
-template <int EOS, class S, class C, int BX, int NT, int HOLD>
+//
+// What bounds it, and what this layout measured per step on 4096^2 (before:
+// 128- and 192-column strips with a wavefront for the halo columns, FP64
+// with the second pull): FP64 367 -> 280 us, FP32 174 -> 156 us.  In FP64 the
+// second pull came from memory, not from L2 (1431 MB fetched per launch
+// against 719 for the pseudopotential kernel): with 12 wavefronts a compute
+// unit it kept the kernel at the memory's rate (336 us), with the rows held
+// at 233 registers and 8 wavefronts it is 280.  FP32 is bound by the vector
+// units (584 -> 500 instructions a row; three rows a turn, after which the
+// held rows are back in their registers).  LEAN as for tile_p2.
+template <int EOS, class S, class C, int BX, int NT, int HOLD, int LEAN>
 __device__ __forceinline__ void tile_fe2(const S* __restrict__ src, S* __restrict__ dst,
                                          const KParams<C>& kp, unsigned* __restrict__ flags,
-                                         int x0, int y0) {
-  __shared__ C rho1[4][BX + 10];  // columns x0-5 .. x0+w+4 (index off + 5)
-  __shared__ C mu1[4][BX + 8];    // x0-4 .. x0+w+3 (off + 4)
-  __shared__ C xb[6][BX + 6];     // x-moving g*1 of one row, x0-3 .. x0+w+2 (off + 3)
-  __shared__ C rho2[4][BX + 4];   // x0-2 .. x0+w+1 (off + 2)
-  __shared__ C mu2[4][BX + 2];    // x0-1 .. x0+w (off + 1)
+                                         int x0, int y0, int sw) {
+  constexpr int SP = LEAN ? 0 : 1;  // the spare element
+  __shared__ C rho1[4][BX + 10 + SP];  // columns x0-5 .. x0+w+4 (index off + 5)
+  __shared__ C mu1[4][BX + 8 + SP];    // x0-4 .. x0+w+3 (off + 4)
+  __shared__ C xb[6][BX + 6 + SP];     // x-moving g*1 of one row, x0-3 .. x0+w+2 (off + 3)
+  __shared__ C rho2[4][BX + 4 + SP];   // x0-2 .. x0+w+1 (off + 2)
+  __shared__ C mu2[4][BX + 2 + SP];    // x0-1 .. x0+w (off + 1)
   __shared__ unsigned s_flag;
   if (threadIdx.x == 0) s_flag = 0u;
-  const int nx = kp.nx, ny = kp.ny;
-  const int w = min(BX, nx - x0);
+  const int nx = kp.nx, ny = kp.ny, pitch = kp.rowpitch;
+  const int w = min(sw, nx - x0);
   const int ly = min(kp.LY, ny - y0);
   const int t = threadIdx.x;
   const bool mainl = t < BX;
@@ -1121,12 +1290,20 @@ __device__ __forceinline__ void tile_fe2(const S* __restrict__ src, S* __restric
   const bool dC = own || (!mainl && h < 6);
   const bool dD = own || (!mainl && h < 4);
   const bool dE = own || (!mainl && h < 2);
+  // Every lane takes part in every stage (straight-line code): a lane without
+  // a column there reads the strip's first one and writes to the spare
+  // element past the row.
+  const int wA = dA ? off + 5 : BX + 10, wB = dB ? off + 4 : BX + 8, wC = dC ? off + 3 : BX + 6;
+  const int wD = dD ? off + 2 : BX + 4, wE = dE ? off + 1 : BX + 2;
+  const int jB = dB ? off : 0, jC = dC ? off : 0, jD = dD ? off : 0, jE = dE ? off : 0;
+  const unsigned long long lanes = __ballot(own);
   const int x = wrapi(x0 + (dA ? off : 0), nx);
   const int xm = (x == 0) ? nx - 1 : x - 1;
   const int xp = (x == nx - 1) ? 0 : x + 1;
-  const int cm = colo(xm), c0 = colo(x), cp = colo(xp);
+  const unsigned cm = colo(xm) * (unsigned)sizeof(S), c0 = colo(x) * (unsigned)sizeof(S),
+                 cp = colo(xp) * (unsigned)sizeof(S);
 
-  unsigned fl = 0;
+  SweepFlags<!LEAN> fl;
   // second step: complete pulled rows R0 (collided at this iteration), R1,
   // R2 (completed at this iteration); partial rows: p1 = row r-4 before the
   // deposit (f0 f1 f3 f2 f5 f6), p2 = row r-3 (f2 f5 f6)
@@ -1137,10 +1314,20 @@ __device__ __forceinline__ void tile_fe2(const S* __restrict__ src, S* __restric
 #pragma unroll
   for (int i = 0; i < 9; ++i) R0[i] = R1[i] = R2[i] = C(0);
 
-  auto rowoff = [&](int y) { return wrapi(y, ny) * kp.rowpitch; };
-  auto pull = [&](int y, C g[9]) {
-    const int r0 = rowoff(y), rm = rowoff(y - 1), rp = rowoff(y + 1);
-    pull9<S, C, NT>(src, rm, r0, rp, cm, c0, cp, g);
+  // offsets of rows r-3 .. r+2 (uniform, so scalar)
+  const int rend = ny * pitch;
+  auto row_after = [&](int o) { return o + pitch == rend ? 0 : o + pitch; };
+  int o[6];
+  o[0] = wrapi(y0 - 8, ny) * pitch;
+#pragma unroll
+  for (int i = 1; i < 6; ++i) o[i] = row_after(o[i - 1]);
+  auto stage_end = [&]() {
+    if constexpr (!LEAN) __builtin_amdgcn_sched_barrier(0);
+  };
+  auto stage_sync = [&]() {
+    stage_end();
+    __syncthreads();
+    stage_end();
   };
   auto mu_at = [&](const C* bot, const C* mid, const C* top, int j) {
     C v[9];
@@ -1149,59 +1336,66 @@ __device__ __forceinline__ void tile_fe2(const S* __restrict__ src, S* __restric
   };
 
   const int ra = y0 - 5;  // first-step row fetched at k = 0
-  const int niter = ly + 11;
+  const int rend_it = ra + ly + 11;
   C gA[9];         // row r, fetched one iteration ahead
   C h1[9], h2[9];  // HOLD: rows r-1 and r-2 as A pulled them
   C gC[9];         // !HOLD: row r-2, pulled again at the start of phase 1
-  pull(ra, gA);
-  for (int k = 0; k < niter; ++k) {
-    const int r = ra + k;
+  pull9_rows<S, C, NT>(src, o[2], o[3], o[4], cm, c0, cp, gA);
+  int r = ra;
+  auto do_row = [&]() {
     // ---- phase 0: A(r), D(r-3)
     C g[9];
-    if (r <= y0 + ly + 4 && dA) {
+    if (!LEAN || (r <= y0 + ly + 4 && dA)) {
 #pragma unroll
       for (int i = 0; i < 9; ++i) g[i] = gA[i];
       const C dr = sum9(g);
-      if (own) fl |= domain_flags<MODEL_FE, EOS>(kp.rho_ref + dr, kp);
-      rho1[r & 3][off + 5] = dr;
+      if constexpr (!LEAN) pin9(g);
+      fl.template check<MODEL_FE, EOS>(kp.rho_ref + dr, kp, lanes);
+      rho1[r & 3][wA] = dr;
     }
-    if (r - 3 >= y0 - 3 && r - 3 <= y0 + ly + 2 && dD) {
-      const int j = off + 3;
+    stage_end();
+    if (!LEAN || (r - 3 >= y0 - 3 && r - 3 <= y0 + ly + 2 && dD)) {
+      const int j = jD + 3;
       // f_4(x, r-4) = g*1_4(x, r-3), f_7 from x+1, f_8 from x-1
       R2[0] = p1_0; R2[1] = p1_1; R2[2] = p1_2; R2[3] = p1_3;
       R2[4] = k4; R2[5] = p1_5; R2[6] = p1_6;
       R2[7] = xb[5][j + 1];
       R2[8] = xb[2][j - 1];
-      if (r - 4 >= y0 - 2) {
-        const C dq = sum9(R2);
-        if (own) fl |= domain_flags<MODEL_FE, EOS>(kp.rho_ref + dq, kp);
-        rho2[(r - 4) & 3][off + 2] = dq;
+      // row r-4: complete from y0-2 on
+      C dq = sum9(R2);
+      if constexpr (!LEAN) {
+        pin(dq);
+        pin9(R2);
       }
+      if (!LEAN || r - 4 >= y0 - 2)
+        fl.template check<MODEL_FE, EOS>(kp.rho_ref + dq, kp, r - 4 >= y0 - 2 ? lanes : 0ull);
+      rho2[(r - 4) & 3][wD] = dq;
       // row r-3: f_0 own, f_1 from x-1, f_3 from x+1 (f_2 f_5 f_6 already in)
       p1_0 = k0; p1_1 = xb[0][j - 1]; p1_3 = xb[3][j + 1];
       p1_2 = p2_2; p1_5 = p2_5; p1_6 = p2_6;
       // row r-2: f_2 own, f_5 from x-1, f_6 from x+1
       p2_2 = k2; p2_5 = xb[1][j - 1]; p2_6 = xb[4][j + 1];
     }
-    __syncthreads();
+    stage_sync();
     // ---- phase 1: B(r-1), E(r-5)
-    if constexpr (HOLD) pull(r + 1, gA);
-    else pull(r - 2, gC);
-    if (r - 1 >= y0 - 4 && r - 1 <= y0 + ly + 3 && dB)
-      mu1[(r - 1) & 3][off + 4] = mu_at(rho1[(r - 2) & 3], rho1[(r - 1) & 3], rho1[r & 3], off + 5);
-    if (r - 5 >= y0 - 1 && r - 5 <= y0 + ly && dE)
-      mu2[(r - 5) & 3][off + 1] = mu_at(rho2[(r - 6) & 3], rho2[(r - 5) & 3], rho2[(r - 4) & 3], off + 2);
-    __syncthreads();
+    if constexpr (HOLD) pull9_rows<S, C, NT>(src, o[3], o[4], o[5], cm, c0, cp, gA);
+    else pull9_rows<S, C, NT>(src, o[0], o[1], o[2], cm, c0, cp, gC);
+    if (!LEAN || (r - 1 >= y0 - 4 && r - 1 <= y0 + ly + 3 && dB))
+      mu1[(r - 1) & 3][wB] = mu_at(rho1[(r - 2) & 3], rho1[(r - 1) & 3], rho1[r & 3], jB + 5);
+    stage_end();
+    if (!LEAN || (r - 5 >= y0 - 1 && r - 5 <= y0 + ly && dE))
+      mu2[(r - 5) & 3][wE] = mu_at(rho2[(r - 6) & 3], rho2[(r - 5) & 3], rho2[(r - 4) & 3], jE + 2);
+    stage_sync();
     // ---- phase 2: C(r-2), F(r-6)
     const int c = r - 2;
-    if (c >= y0 - 3 && c <= y0 + ly + 2 && dC) {
+    if (!LEAN || (c >= y0 - 3 && c <= y0 + ly + 2 && dC)) {
       C g[9];
 #pragma unroll
       for (int i = 0; i < 9; ++i) g[i] = HOLD ? h2[i] : gC[i];
       const C d0 = sum9(g);
       C v[9], m[9];
-      gather(rho1[(c - 1) & 3], rho1[c & 3], rho1[(c + 1) & 3], off + 5, v);
-      gather(mu1[(c - 1) & 3], mu1[c & 3], mu1[(c + 1) & 3], off + 4, m);
+      gather(rho1[(c - 1) & 3], rho1[c & 3], rho1[(c + 1) & 3], jC + 5, v);
+      gather(mu1[(c - 1) & 3], mu1[c & 3], mu1[(c + 1) & 3], jC + 4, m);
       C grx, gry, gmx, gmy;
       grad_sum(v, grx, gry);
       grad_sum(m, gmx, gmy);
@@ -1213,8 +1407,11 @@ __device__ __forceinline__ void tile_fe2(const S* __restrict__ src, S* __restric
       // the single-step kernel stores the first step's output and loads it
       // back: round to the storage type the same way
 #pragma unroll
-      for (int i = 0; i < 9; ++i) g[i] = (C)(S)g[i];
-      const int j = off + 3;
+      for (int i = 0; i < 9; ++i) {
+        g[i] = (C)(S)g[i];
+        if constexpr (!LEAN) pin(g[i]);
+      }
+      const int j = wC;
       xb[0][j] = g[1];
       xb[1][j] = g[5];
       xb[2][j] = g[8];
@@ -1225,11 +1422,12 @@ __device__ __forceinline__ void tile_fe2(const S* __restrict__ src, S* __restric
       k2 = g[2];
       k4 = g[4];
     }
+    stage_end();
     const int b = r - 6;
-    if (b >= y0 && own) {
+    if (!LEAN || (b >= y0 && own)) {
       C v[9], m[9];
-      gather(rho2[(b - 1) & 3], rho2[b & 3], rho2[(b + 1) & 3], off + 2, v);
-      gather(mu2[(b - 1) & 3], mu2[b & 3], mu2[(b + 1) & 3], off + 1, m);
+      gather(rho2[(b - 1) & 3], rho2[b & 3], rho2[(b + 1) & 3], jE + 2, v);
+      gather(mu2[(b - 1) & 3], mu2[b & 3], mu2[(b + 1) & 3], jE + 1, m);
       C grx, gry, gmx, gmy;
       grad_sum(v, grx, gry);
       grad_sum(m, gmx, gmy);
@@ -1239,12 +1437,13 @@ __device__ __forceinline__ void tile_fe2(const S* __restrict__ src, S* __restric
       const C Fy = -rho * gmy + kp.fy;
       C ux, uy;
       collide<MODEL_FE>(R0, d0, rho, Fx, Fy, grx, gry, C(0), C(0), kp, ux, uy);
-      const int o = b * kp.rowpitch + c0;
-#pragma unroll
-      for (int i = 0; i < 9; ++i) st<NT>(&dst[o + 64 * i], (S)R0[i]);
+      if (b >= y0 && own) store9_row<NT>(dst, b * pitch, c0, R0);
     }
-    if constexpr (!HOLD) pull(r + 1, gA);
-    __syncthreads();
+    if constexpr (!HOLD) pull9_rows<S, C, NT>(src, o[3], o[4], o[5], cm, c0, cp, gA);
+    stage_sync();
+#pragma unroll
+    for (int i = 0; i < 5; ++i) o[i] = o[i + 1];
+    o[5] = row_after(o[5]);
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
       R0[i] = R1[i];
@@ -1254,8 +1453,18 @@ __device__ __forceinline__ void tile_fe2(const S* __restrict__ src, S* __restric
         h1[i] = g[i];
       }
     }
+    r = __builtin_amdgcn_readfirstlane(r + 1);
+  };
+  while (r < rend_it) {
+    do_row();
+    if constexpr (!LEAN) {
+      if (r == rend_it) break;
+      do_row();
+      if (r == rend_it) break;
+      do_row();
+    }
   }
-  commit_flags(fl, flags, &s_flag);
+  commit_flags(fl.bits(), flags, &s_flag);
 }
 
 // Free-energy step on one tile.  GEN as for tile_p; GEN = 3 adds the A term
@@ -1904,27 +2113,26 @@ void k_step_p_pipe(const S* __restrict__ src, S* __restrict__ dst, const KParams
                                  (tile / kp.nstrips) * kp.LY);
 }
 
-// Two pseudopotential steps per launch (tile_p2): BX + 64 threads.
+// Two pseudopotential steps per launch (tile_p2) on strips of sw <= BX - 16
+// columns, the workgroup's last lanes on the halo columns.
 template <int EOS, class S, class C, int BX, int NT>
-__global__ __launch_bounds__(BX + 64) void k_step2_p(const S* __restrict__ src,
-                                                     S* __restrict__ dst, const KParams<C> kp,
-                                                     unsigned* __restrict__ flags) {
+__global__ __launch_bounds__(BX) __attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 2 : 4)))
+void k_step2_p(const S* __restrict__ src, S* __restrict__ dst, const KParams<C> kp,
+               unsigned* __restrict__ flags, int sw) {
   const int tile = tile_index(kp.xcd_remap);
-  tile_p2<EOS, S, C, BX, NT, sizeof(S) == 8 ? 1 : 0>(src, dst, kp, flags,
-                                                   (tile % kp.nstrips) * BX,
-                                                   (tile / kp.nstrips) * kp.LY);
+  tile_p2<EOS, S, C, BX - 16, NT, sizeof(S) == 8 ? 1 : 0, 0>(
+      src, dst, kp, flags, (tile % kp.nstrips) * sw, (tile / kp.nstrips) * kp.LY, sw);
 }
 
-// Two free-energy steps per launch (tile_fe2): BX + 64 threads.
-// Non-temporal stores; FP32 keeps the first step's rows (HOLD).
+// Two free-energy steps per launch (tile_fe2), as k_step2_p; non-temporal
+// stores.
 template <int EOS, class S, class C, int BX>
-__global__ __launch_bounds__(BX + 64) void k_step2_fe(const S* __restrict__ src,
-                                                      S* __restrict__ dst, const KParams<C> kp,
-                                                      unsigned* __restrict__ flags) {
+__global__ __launch_bounds__(BX) __attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 2 : 3)))
+void k_step2_fe(const S* __restrict__ src, S* __restrict__ dst, const KParams<C> kp,
+                unsigned* __restrict__ flags, int sw) {
   const int tile = tile_index(kp.xcd_remap);
-  tile_fe2<EOS, S, C, BX, 1, sizeof(S) == 4 ? 1 : 0>(src, dst, kp, flags,
-                                                   (tile % kp.nstrips) * BX,
-                                                   (tile / kp.nstrips) * kp.LY);
+  tile_fe2<EOS, S, C, BX - 16, 1, 1, 0>(src, dst, kp, flags, (tile % kp.nstrips) * sw,
+                                       (tile / kp.nstrips) * kp.LY, sw);
 }
 
 template <int EOS, class S, class C, int BX, int NT, int WPE, int GEN = 0>
@@ -2020,8 +2228,9 @@ void k_batch_step(const BatchTile* __restrict__ tiles, const int* __restrict__ c
   }
 }
 
-// Two steps of every tile in the table (tile_p2 / tile_fe2, BX + 64 threads,
-// the same row schedules and register choices as k_step2_p / k_step2_fe),
+// Two steps of every tile in the table (tile_p2 / tile_fe2 in their LEAN form,
+// BX + 64 threads: the tiles' 256 columns leave the halo lanes a wavefront of
+// their own),
 // walking the table as k_batch_step does.  The table holds the single-step
 // kernel's 256-column tiles, so one table serves both kernels; the
 // free-energy kernel runs 128-column strips (in FP64 the 256-column one fits
@@ -2033,6 +2242,7 @@ constexpr int batch2_bx() { return MODEL == MODEL_P ? 256 : 128; }
 
 template <int MODEL, int EOS, class S, class C>
 __global__ __launch_bounds__(batch2_bx<MODEL>() + 64)
+__attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 3 : MODEL == MODEL_P ? 7 : 4)))
 void k_batch_step2(const BatchTile* __restrict__ tiles, const int* __restrict__ count,
                    const InstDesc<C>* __restrict__ inst, int parity) {
   constexpr int BX = batch2_bx<MODEL>();
@@ -2046,10 +2256,16 @@ void k_batch_step2(const BatchTile* __restrict__ tiles, const int* __restrict__ 
     if (x0 >= d->kp.nx) continue;  // the lattice ends in the first half
     const S* src = (const S*)(parity ? d->fB : d->fA);
     S* dst = (S*)(parity ? d->fA : d->fB);
-    if constexpr (MODEL == MODEL_P)
-      tile_p2<EOS, S, C, BX, 1, sizeof(S) == 8 ? 1 : 0>(src, dst, d->kp, d->flags, x0, bt.y0);
-    else
-      tile_fe2<EOS, S, C, BX, 1, sizeof(S) == 4 ? 1 : 0>(src, dst, d->kp, d->flags, x0, bt.y0);
+    if constexpr (MODEL == MODEL_P) {
+      // the parameters by value: behind the pointer the stores could alias
+      // them, and every row would load them again (8 x 1024^2 FP64 190 -> 173
+      // us per step; the free-energy kernel has no registers for them)
+      const KParams<C> kp = d->kp;
+      tile_p2<EOS, S, C, BX, 1, sizeof(S) == 8 ? 1 : 0, 1>(src, dst, kp, d->flags, x0, bt.y0, BX);
+    } else {
+      tile_fe2<EOS, S, C, BX, 1, sizeof(S) == 4 ? 1 : 0, 1>(src, dst, d->kp, d->flags, x0, bt.y0,
+                                                            BX);
+    }
     __syncthreads();  // the next tile reuses the LDS rings
   }
 }
@@ -2532,7 +2748,7 @@ struct LaunchCfg {
   int wpe;   // 1: register-capped kernel variant
   int pipe;  // 1: pipelined row loop (pseudopotential)
   int two;   // 1: two steps per launch where the model and options allow
-  int bx2;   // strip width of the two-step kernel: 128, 192 or 256
+  int bx2;   // lanes of a two-step workgroup: 128 or 256 (free energy: 192 too)
   int auto_ly;  // 1: segment height set at the first launch from occupancy
 };
 
@@ -2558,7 +2774,7 @@ struct lbm_ctx {
   LaunchCfg lc;
   PatchPlan pp;
   int nstrips, nseg, xcd_remap;
-  int nstrips2, nseg2, xcd_remap2;  // tiling of the two-step kernel (bx2 strips)
+  int sw2, nstrips2, nseg2, xcd_remap2;  // tiling of the two-step kernel (strips of sw2)
   KParams<double> kd;
   KParams<float> kf;
   // lbm_step replays runs of kGraphSteps steps as HIP graphs, captured on a
@@ -2570,6 +2786,31 @@ struct lbm_ctx {
 };
 
 namespace {
+
+// Two-step strips: a workgroup of `lanes` lanes takes strips of up to
+// lanes - 16 columns, the other lanes the halo columns.  The strips are equal
+// and start on multiples of 16 columns, so that no two workgroups write to
+// one 128-byte line in FP64 (64-byte half line in FP32): on 4096^2 strips at
+// any column cost 296 against 258 us per step in P FP64 and 171 against 142
+// in FP32.
+int two_width(int nx, int lanes) {
+  const int n = (nx + lanes - 17) / (lanes - 16);
+  return ((nx + n - 1) / n + 15) / 16 * 16;
+}
+
+int two_strips(int nx, int lanes) {
+  const int w = two_width(nx, lanes);
+  return (nx + w - 1) / w;
+}
+
+// 256 lanes or 128, whichever leaves fewer lanes idle: both cost the same per
+// lane (P FP64 0.0547 and 0.0557 us per lane column and step at 4096 rows, FE
+// FP64 0.0608 and 0.0610, P FP32 0.0308 and 0.0303, FE FP32 0.0338 and
+// 0.0333); 4096 columns are 18 x 256 against 37 x 128 lanes, 1000 columns
+// 5 x 256 against 9 x 128.
+int two_lanes(int nx) {
+  return two_strips(nx, 128) * 128 < two_strips(nx, 256) * 256 ? 128 : 256;
+}
 
 // Launch-shape resolution: the launch fields of lbm_params where set, else
 // defaults measured on MI355X (4096^2 lattices: 256-column strips,
@@ -2598,16 +2839,12 @@ LaunchCfg resolve_launch(const lbm_params* p) {
     // (in FP64 its four live population rows cost a wave of occupancy)
     lc.pipe = (p->model == LBM_MODEL_P || !fp64) ? 1 : 0;
     // two steps per launch, measured per step on 4096^2: pseudopotential
-    // (256-column strips) 0.338 vs 0.476 ms in FP64 and 0.152 vs 0.233 ms in
-    // FP32; free energy 0.406 vs 0.486 ms in FP64 and 0.178 vs 0.249 ms in
-    // FP32
+    // 0.252 vs 0.476 ms in FP64 and 0.141 vs 0.233 ms in FP32; free energy
+    // 0.280 vs 0.486 ms in FP64 and 0.156 vs 0.249 ms in FP32
     lc.two = 1;
-    // free energy: FP64 128-column strips (192: 0.406 ms, 256: 0.610);
-    // FP32 192-column strips (0.178 ms; 128: 0.192, 256: 0.214)
-    lc.bx2 = p->model == LBM_MODEL_FE ? (fp64 ? 128 : 192) : 256;
+    lc.bx2 = two_lanes(p->nx);
   }
-  // the pseudopotential two-step kernel runs 256-column strips only
-  if (p->model == LBM_MODEL_P) lc.bx2 = 256;
+  if (p->model == LBM_MODEL_P) lc.bx2 = two_lanes(p->nx);
   if (p->boundary == LBM_BOUNDARY_WALLS || p->ax != 0.0 || p->A != 0.0) {
     // walls, the collision drive and A != 0 run in the general kernel:
     // plain row loop, non-temporal stores
@@ -2654,7 +2891,8 @@ void apply_launch(lbm_ctx* c) {
     k->LY = c->lc.ly;
     k->xcd_remap = c->xcd_remap;
   }
-  c->nstrips2 = (c->p.nx + c->lc.bx2 - 1) / c->lc.bx2;
+  c->nstrips2 = two_strips(c->p.nx, c->lc.bx2);
+  c->sw2 = two_width(c->p.nx, c->lc.bx2);
   c->nseg2 = c->nseg;
   const int ntiles2 = c->nstrips2 * c->nseg2;
   c->xcd_remap2 = (ntiles2 >= 64 && ntiles2 % 8 == 0 && !no_remap) ? 1 : 0;
@@ -2711,13 +2949,13 @@ struct PatchCost {
 const PatchCost& patch_cost(const lbm_params& p) {
   static const PatchCost t[2][2][2] = {
       // [model][FP32][GEN]
-      {{{1.05, 1.13, 0.858, 0.737, 0.127, 0.266, 0, 0.53, 25, 0.0212, 24, 16},
+      {{{1.05, 1.13, 0.858, 0.737, 0.127, 0.266, 0, 0.53, 25, 0.0148, 24, 16},
         {2.48, 0.00, 1.070, 0.761, 0.134, 0.182, 0, 0.67, 25, 0.0294, 20, 16}},
-       {{2.65, 0.00, 0.755, 0.552, 0.074, 0.347, 0, 0.17, 20, 0.0092, 32, 32},
+       {{2.65, 0.00, 0.755, 0.552, 0.074, 0.347, 0, 0.17, 20, 0.0077, 32, 32},
         {2.76, 0.00, 0.627, 1.072, 0.086, 0.154, 0, 0.18, 20, 0.0145, 32, 28}}},
-      {{{1.58, 0.35, 1.480, 0.323, 0.165, 0.321, 0, 0.78, 30, 0.0232, 16, 16},
+      {{{1.58, 0.35, 1.480, 0.323, 0.165, 0.321, 0, 0.78, 30, 0.0168, 16, 16},
         {2.22, 1.19, 1.260, 0.813, 0.139, 0.175, 0, 0.93, 33, 0.0300, 16, 16}},
-       {{2.34, 0.00, 1.237, 0.691, 0.050, 0, 0.172, 0.29, 25, 0.0106, 32, 32},
+       {{2.34, 0.00, 1.237, 0.691, 0.050, 0, 0.172, 0.29, 25, 0.0087, 32, 32},
         {0.22, 1.73, 1.960, 0.000, 0.150, 0, 0.152, 0.48, 25, 0.0155, 28, 20}}}};
   return t[p.model == LBM_MODEL_P ? 0 : 1][p.precision == LBM_FP64 ? 0 : 1][needs_gen(p) ? 1 : 0];
 }
@@ -2971,20 +3209,18 @@ void launch_step(lbm_ctx* c, const KParams<C>& kp) {
   else launch_step_bx<MODEL, EOS, S, C, 256>(c, kp);
 }
 
-// Two steps in one launch (periodic lattices): strips of bx2 columns
-// (256, or 128 for the free-energy kernel, whose register budget leaves two
-// 256-column workgroups per CU but four 128-column ones).  The segment
-// height is chosen for this kernel even when a single step is launched
+// Two steps in one launch (periodic lattices), workgroups of bx2 lanes on
+// strips of sw2 columns (two_lanes, two_width).  The segment height is chosen for this kernel even when a single step is launched
 // first (odd step counts), since it carries the run.
 template <int EOS, class S, class C, int BX>
 void tune_two_bx(lbm_ctx* c) {
   if (c->p.model == LBM_MODEL_P) {
-    if constexpr (BX == 256) {
-      if (c->lc.nt) tune_ly(c, k_step2_p<EOS, S, C, BX, 1>, BX + 64, c->nstrips2);
-      else tune_ly(c, k_step2_p<EOS, S, C, BX, 0>, BX + 64, c->nstrips2);
+    if constexpr (BX != 192) {
+      if (c->lc.nt) tune_ly(c, k_step2_p<EOS, S, C, BX, 1>, BX, c->nstrips2);
+      else tune_ly(c, k_step2_p<EOS, S, C, BX, 0>, BX, c->nstrips2);
     }
   } else {
-    tune_ly(c, k_step2_fe<EOS, S, C, BX>, BX + 64, c->nstrips2);
+    tune_ly(c, k_step2_fe<EOS, S, C, BX>, BX, c->nstrips2);
   }
 }
 
@@ -3015,16 +3251,19 @@ void launch_step2_bx(lbm_ctx* c, const KParams<C>& kp_in) {
   const S* src = (const S*)(c->ws + (c->cur ? c->L.fB : c->L.fA));
   S* dst = (S*)(c->ws + (c->cur ? c->L.fA : c->L.fB));
   unsigned* flags = (unsigned*)(c->ws + c->L.flags);
-  dim3 grid(c->nstrips2 * c->nseg2), block(BX + 64);
+  dim3 grid(c->nstrips2 * c->nseg2), block(BX);
   if (c->p.model == LBM_MODEL_P) {
-    if constexpr (BX == 256) {
+    if constexpr (BX != 192) {
       if (c->lc.nt)
-        hipLaunchKernelGGL((k_step2_p<EOS, S, C, BX, 1>), grid, block, 0, c->stream, src, dst, kp, flags);
+        hipLaunchKernelGGL((k_step2_p<EOS, S, C, BX, 1>), grid, block, 0, c->stream, src, dst, kp,
+                           flags, c->sw2);
       else
-        hipLaunchKernelGGL((k_step2_p<EOS, S, C, BX, 0>), grid, block, 0, c->stream, src, dst, kp, flags);
+        hipLaunchKernelGGL((k_step2_p<EOS, S, C, BX, 0>), grid, block, 0, c->stream, src, dst, kp,
+                           flags, c->sw2);
     }
   } else {
-    hipLaunchKernelGGL((k_step2_fe<EOS, S, C, BX>), grid, block, 0, c->stream, src, dst, kp, flags);
+    hipLaunchKernelGGL((k_step2_fe<EOS, S, C, BX>), grid, block, 0, c->stream, src, dst, kp, flags,
+                       c->sw2);
   }
   c->cur ^= 1;
 }
@@ -3037,8 +3276,14 @@ void launch_step2(lbm_ctx* c, const KParams<C>& kp) {
   else launch_step2_bx<EOS, S, C, 256>(c, kp);
 }
 
+// The two-step kernels address a column by its byte offset in the row, in 32
+// bits.
+bool two_addressable(const lbm_ctx* c) {
+  return (int64_t)c->kd.rowpitch * (c->p.precision == LBM_FP64 ? 8 : 4) < (int64_t)1 << 32;
+}
+
 bool two_step_ok(const lbm_ctx* c) {
-  return c->lc.two && !needs_gen(c->p) && c->lc.bx == 256;
+  return c->lc.two && !needs_gen(c->p) && c->lc.bx == 256 && two_addressable(c);
 }
 
 // One patch launch of m <= pp.ps.steps steps.
@@ -3455,8 +3700,8 @@ lbm_status lbm_launch_info(const lbm_ctx* c, lbm_launch* out) {
   }
   const bool two = two_step_ok(c);
   out->steps_per_launch = two ? 2 : 1;
-  out->strip = two ? c->lc.bx2 : c->lc.bx;
-  out->threads = two ? c->lc.bx2 + 64 : c->lc.bx;
+  out->strip = two ? c->sw2 : c->lc.bx;
+  out->threads = two ? c->lc.bx2 : c->lc.bx;
   if (!c->lc.auto_ly) {
     out->segment = c->lc.ly;
     out->workgroups = two ? c->nstrips2 * c->nseg2 : c->nstrips * c->nseg;
@@ -3795,7 +4040,9 @@ void run_family(lbm_batch* b, int f, int steps) {
 // A problem takes two steps per launch in a batch when its launch
 // configuration asks for them and its tiles are 256-column strips (the
 // two-step row schedules need the halo wavefront beside the strip).
-int batch_two(const lbm_ctx* c) { return c->lc.two && c->lc.bx == 256 ? 1 : 0; }
+int batch_two(const lbm_ctx* c) {
+  return c->lc.two && c->lc.bx == 256 && two_addressable(c) ? 1 : 0;
+}
 
 // Two-step launches of a two-step group in a chunk of `steps` (even) steps:
 // the last two steps are single (the last one checking), and the launch
@@ -3889,7 +4136,10 @@ bool choose_families(lbm_batch* b) {
       else it->count += 1;
     }
     PatchChoice c{};
-    if (!cls.empty() && N < 1.2e7)  // beyond, the strips always win
+    // beyond, the strips win: P 3.1 M nodes 80 us per step (strips 97) in FP64
+    // and 36.7 (37.1) in FP32, 4.2 M 110 (100) and 49 (45); FE 1.6 M 52 (53)
+    // and 29.7 (32.1), 2.1 M 70 (66) and 37 (34)
+    if (!cls.empty() && N < (f < 2 ? 3.3e6 : 1.7e6))
       c = choose_patch(cls, family_limit_us(f < 2 ? LBM_MODEL_P : LBM_MODEL_FE, b->fp64, N),
                        kPatchTiles);
     b->fam[f].c = c;

@@ -2295,6 +2295,44 @@ __global__ __launch_bounds__(1024) void k_batch_patch(const BatchTile* __restric
                                            &s_flag, ck, s_du);
 }
 
+// Smallest initial density of a block's share and whether any value there is
+// outside the EOS domain (the tests of lbm.h: finite, positive, b rho / 4 or
+// b rho below 1): what starting a lattice has to know before its storage
+// shift can be chosen.  One read of the field; copied to the host and scanned
+// there, a 4096^2 lattice took 57 ms to start (0.44 now, the storage of the
+// first state included), 32 lattices of 64^2 .. 512^2 6.6 ms (0.6), 128 of
+// 64 x 8 and 128^2 5.7 ms (1.5).
+struct Rho0Check {
+  double rmin;
+  unsigned long long bad;
+};
+
+__global__ __launch_bounds__(256) void k_rho0_check(const double* __restrict__ rho0, size_t n,
+                                                    double b, int cs,
+                                                    Rho0Check* __restrict__ out) {
+  __shared__ double s_min[4];
+  __shared__ int s_bad[4];
+  double m = INFINITY;
+  bool bad = false;
+  for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
+    const double r = rho0[i];
+    const double lim = cs ? b * r * 0.25 : b * r;
+    bad |= !__builtin_isfinite(r) || !(lim < 1.0) || !(r > 0.0);
+    m = fmin(m, r);
+  }
+  for (int off = 32; off > 0; off >>= 1) m = fmin(m, __shfl_xor(m, off, 64));
+  const bool any = __ballot(bad) != 0ull;
+  if ((threadIdx.x & 63) == 0) {
+    s_min[threadIdx.x >> 6] = m;
+    s_bad[threadIdx.x >> 6] = any;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    out[blockIdx.x].rmin = fmin(fmin(s_min[0], s_min[1]), fmin(s_min[2], s_min[3]));
+    out[blockIdx.x].bad = s_bad[0] | s_bad[1] | s_bad[2] | s_bad[3];
+  }
+}
+
 // ---- initial state ------------------------------------------------------------
 // Stored g*_i(x) = f^eq_i(rho0(x + c_i), 0) - s_i, so that the first pull
 // yields f_i(x) = f^eq_i(rho0(x), 0) (Eq. 4: w_i rho; Eq. 20: rho delta_i0).
@@ -3395,19 +3433,75 @@ void observe_dispatch_prec(lbm_ctx* c, int cx, int cy, double* r, double* ux, do
     launch_observe<MODEL, EOS, float>(c, cx, cy, r, ux, uy);
 }
 
-// Context set-up shared by lbm_init and the batch: validation already done,
-// rho0 checked on the host (hrho0), workspace carved.
-lbm_status ctx_setup(const lbm_params* p, void* d_workspace, const double* d_rho0,
-                     const std::vector<double>& hrho0, hipStream_t stream, lbm_ctx** out) {
-  size_t N = (size_t)p->nx * p->ny;
-  double rmin = INFINITY;
-  for (size_t n = 0; n < N; ++n) {
-    double r = hrho0[n];
-    if (!std::isfinite(r)) return LBM_ERR_EOS_DOMAIN;
-    double lim = (p->eos == LBM_EOS_CS) ? p->b * r / 4.0 : p->b * r;
-    if (!(lim < 1.0) || !(r > 0.0)) return LBM_ERR_EOS_DOMAIN;
-    rmin = std::min(rmin, r);
+lbm_status read_host(const double* d, size_t n, hipStream_t stream, std::vector<double>& h) {
+  h.resize(n);
+  if (hipMemcpyAsync(h.data(), d, n * sizeof(double), hipMemcpyDeviceToHost, stream) != hipSuccess)
+    return LBM_ERR_HIP;
+  if (hipStreamSynchronize(stream) != hipSuccess) return LBM_ERR_HIP;
+  return LBM_OK;
+}
+
+// What a lattice needs to know of its initial density.
+struct Rho0Info {
+  double rmin;  // smallest value
+  double ave;   // mean for the collision drive
+};
+
+// Check the initial densities of n lattices and find their smallest values:
+// one kernel per lattice, one copy for all.  `scratch` (a workspace that
+// holds nothing yet) takes the blocks' results, 16 bytes per block, at most
+// one block per 2048 nodes or one per lattice.  LBM_ERR_EOS_DOMAIN if a value
+// is outside the domain.
+lbm_status rho0_info(int n, const lbm_params* p, const double* const* d_rho0, char* scratch,
+                     hipStream_t stream, std::vector<Rho0Info>& out) {
+  std::vector<int> first(n + 1, 0);
+  for (int i = 0; i < n; ++i) {
+    const size_t N = (size_t)p[i].nx * p[i].ny;
+    first[i + 1] = first[i] + (int)std::min<size_t>((N + 2047) / 2048, 1024);
   }
+  Rho0Check* d = (Rho0Check*)scratch;
+  for (int i = 0; i < n; ++i)
+    hipLaunchKernelGGL(k_rho0_check, dim3(first[i + 1] - first[i]), dim3(256), 0, stream,
+                       d_rho0[i], (size_t)p[i].nx * p[i].ny, p[i].b,
+                       p[i].eos == LBM_EOS_CS ? 1 : 0, d + first[i]);
+  std::vector<Rho0Check> h(first[n]);
+  if (hipGetLastError() != hipSuccess ||
+      hipMemcpyAsync(h.data(), d, h.size() * sizeof(Rho0Check), hipMemcpyDeviceToHost, stream) !=
+          hipSuccess ||
+      hipStreamSynchronize(stream) != hipSuccess)
+    return LBM_ERR_HIP;
+  out.assign(n, Rho0Info{INFINITY, 0.0});
+  for (int i = 0; i < n; ++i)
+    for (int k = first[i]; k < first[i + 1]; ++k) {
+      if (h[k].bad) return LBM_ERR_EOS_DOMAIN;
+      out[i].rmin = std::min(out[i].rmin, h[k].rmin);
+    }
+  std::vector<double> v;
+  for (int i = 0; i < n; ++i) {
+    if (p[i].rho_ave > 0.0 || p[i].ax == 0.0) {
+      out[i].ave = std::max(p[i].rho_ave, 0.0);  // without the drive it has no part
+      continue;
+    }
+    // mean initial density for the collision drive: compensated sum, in the
+    // order of the nodes
+    const size_t N = (size_t)p[i].nx * p[i].ny;
+    const lbm_status st = read_host(d_rho0[i], N, stream, v);
+    if (st != LBM_OK) return st;
+    double s = 0.0, e = 0.0;
+    for (size_t k = 0; k < N; ++k) {
+      const double t = s + v[k];
+      e += (std::fabs(s) >= std::fabs(v[k])) ? (s - t) + v[k] : (v[k] - t) + s;
+      s = t;
+    }
+    out[i].ave = (s + e) / (double)N;
+  }
+  return LBM_OK;
+}
+
+// Context set-up shared by lbm_init and the batch: validation already done,
+// rho0 checked (info), workspace carved.
+lbm_status ctx_setup(const lbm_params* p, void* d_workspace, const double* d_rho0,
+                     const Rho0Info& info, hipStream_t stream, lbm_ctx** out) {
   lbm_ctx* c = new (std::nothrow) lbm_ctx();
   if (!c) return LBM_ERR_INVALID_ARG;
   c->p = *p;
@@ -3418,16 +3512,7 @@ lbm_status ctx_setup(const lbm_params* p, void* d_workspace, const double* d_rho
   c->step = 0;
   c->have_prev = 0;
   c->rho_ref = 0.0;
-  {
-    // mean initial density for the collision drive: compensated sum
-    double s = 0.0, e = 0.0;
-    for (size_t n = 0; n < N; ++n) {
-      double t = s + hrho0[n];
-      e += (std::fabs(s) >= std::fabs(hrho0[n])) ? (s - t) + hrho0[n] : (hrho0[n] - t) + s;
-      s = t;
-    }
-    c->rho_ave = (p->rho_ave > 0.0) ? p->rho_ave : (s + e) / (double)N;
-  }
+  c->rho_ave = info.ave;
   if (p->precision == LBM_FP32_SHIFTED) {
     // Storage shift f^eq(rho_ref, 0) (w_i rho_ref for P, rho_ref delta_i0 for
     // FE).  The default reference is the smallest initial density: the
@@ -3437,7 +3522,7 @@ lbm_status ctx_setup(const lbm_params* p, void* d_workspace, const double* d_rho
     // 2^-24 rho_ref per step).  Round rho_ref so that rho_ref / 36 carries
     // at most 20 significant bits: then w_i rho_ref, their sum and M s are
     // all exact in float and the deviations carry no constant bias.
-    double want = (p->rho_ref > 0.0) ? p->rho_ref : rmin;
+    double want = (p->rho_ref > 0.0) ? p->rho_ref : info.rmin;
     double q = want / 36.0;
     int ex;
     double m = frexp(q, &ex);
@@ -3464,14 +3549,6 @@ lbm_status ctx_setup(const lbm_params* p, void* d_workspace, const double* d_rho
     return LBM_ERR_HIP;
   }
   *out = c;
-  return LBM_OK;
-}
-
-lbm_status read_host(const double* d, size_t n, hipStream_t stream, std::vector<double>& h) {
-  h.resize(n);
-  if (hipMemcpyAsync(h.data(), d, n * sizeof(double), hipMemcpyDeviceToHost, stream) != hipSuccess)
-    return LBM_ERR_HIP;
-  if (hipStreamSynchronize(stream) != hipSuccess) return LBM_ERR_HIP;
   return LBM_OK;
 }
 
@@ -3602,9 +3679,9 @@ lbm_status lbm_init(const lbm_params* p, void* d_workspace, size_t bytes,
   if (!d_workspace || bytes < L.total || ((uintptr_t)d_workspace % kAlign) != 0)
     return LBM_ERR_WORKSPACE;
   hipStream_t stream = (hipStream_t)hip_stream;
-  std::vector<double> h;
-  if ((st = read_host(d_rho0, (size_t)p->nx * p->ny, stream, h)) != LBM_OK) return st;
-  if ((st = ctx_setup(p, d_workspace, d_rho0, h, stream, out)) != LBM_OK) return st;
+  std::vector<Rho0Info> info;
+  if ((st = rho0_info(1, p, &d_rho0, (char*)d_workspace, stream, info)) != LBM_OK) return st;
+  if ((st = ctx_setup(p, d_workspace, d_rho0, info[0], stream, out)) != LBM_OK) return st;
   (*out)->pp = plan_patch(*p);
   return LBM_OK;
 }
@@ -3719,8 +3796,8 @@ lbm_status lbm_autotune(const lbm_params* p, void* d_workspace, size_t bytes,
   if (!d_workspace || bytes < L.total || ((uintptr_t)d_workspace % kAlign) != 0)
     return LBM_ERR_WORKSPACE;
   hipStream_t stream = (hipStream_t)hip_stream;
-  std::vector<double> h;
-  if ((st = read_host(d_rho0, (size_t)p->nx * p->ny, stream, h)) != LBM_OK) return st;
+  std::vector<Rho0Info> info;
+  if ((st = rho0_info(1, p, &d_rho0, (char*)d_workspace, stream, info)) != LBM_OK) return st;
   const bool fp64 = p->precision == LBM_FP64;
   std::vector<int> bxs = {64, 256};
   // tile_y 0: the occupancy-derived one-round segment height
@@ -3744,7 +3821,7 @@ lbm_status lbm_autotune(const lbm_params* p, void* d_workspace, size_t bytes,
   lbm_params bp = *p;
   auto time_shape = [&](const lbm_params& q, bool patch) {
     lbm_ctx* c = nullptr;
-    lbm_status r = ctx_setup(&q, d_workspace, d_rho0, h, stream, &c);
+    lbm_status r = ctx_setup(&q, d_workspace, d_rho0, info[0], stream, &c);
     if (r != LBM_OK) return r;
     if (patch) c->pp = plan_patch(q);
     advance(c, 2);  // warm-up (and first-touch of the second buffer)
@@ -4443,14 +4520,14 @@ lbm_status lbm_batch_create(int32_t n, const lbm_params* p, const double* const*
   b->graph = nullptr;
   b->graph_steps = 0;
   b->inst.resize(n);
-  std::vector<double> h;
+  std::vector<Rho0Info> info;
+  st = rho0_info(n, p, d_rho0, b->ws, stream, info);
   for (int i = 0; i < n && st == LBM_OK; ++i) {
     BatchInst& I = b->inst[i];
     I = BatchInst{nullptr, B.chk_off[i], LBM_BATCH_ACTIVE, 0, INFINITY, INFINITY, 0, 0, 0u,
                   INT64_MAX, -1, p[i].tile_y <= 0 ? 1 : 0, patch_allowed(p[i]) ? 1 : 0, 0,
                   PatchShape{}};
-    st = read_host(d_rho0[i], (size_t)p[i].nx * p[i].ny, stream, h);
-    if (st == LBM_OK) st = ctx_setup(&p[i], b->ws + B.inst_off[i], d_rho0[i], h, stream, &I.ctx);
+    st = ctx_setup(&p[i], b->ws + B.inst_off[i], d_rho0[i], info[i], stream, &I.ctx);
     // half-empty 256-column strips with two steps per launch beat whole
     // 64-column ones in a batch (128^2 FP32: P 0.0196 against 0.0245 ns per
     // node update, FE 0.0259 against 0.0306)

@@ -256,8 +256,15 @@ def build_problems(tuples, sizes, precision, guesses=None, tiles=None):
 # group from its active lattices at every retirement.  Fixed heights are
 # not candidates: timed on a full class, the best of them beats the
 # automatic height by a few per cent, but it stays when the class has
-# retired down to a few lattices, where it is several times slower.
-TILE_CANDIDATES = ((64, 0), (256, 0))
+# retired down to a few lattices, where it is several times slower.  Strip
+# width 0: the batch chooses between strips and patches from all its active
+# lattices (30000 lockstep steps on lattices of 64^2 .. 512^2: 16 tuples 1.73
+# -> 1.11 s, 64 tuples 4.13 -> 3.96 s, 256 tuples 13.6 s both ways).
+TILE_CANDIDATES = ((0, 0), (64, 0), (256, 0))
+# an explicit width has to beat the batch's own choice by this factor on the
+# full class, because it rules patches out when the class has retired to a few
+# lattices
+TILE_MARGIN = 0.95
 
 
 def class_counts(tuples, sizes):
@@ -282,8 +289,8 @@ def autotune_batch_tiles(precision=lbm.FP32_SHIFTED, sizes=SIZES, steps=100, nod
     a run, the last steps of an interval are single steps), timed by the
     batch's own GPU clock (lbm_batch_stats).  Strips of 256 columns (two
     steps per launch) are tried where nx >= 128; the least GPU time per node
-    update wins.  Returns {(model, nx, ny): (tile_x, tile_y)} and the
-    timings."""
+    update wins, an explicit width only by more than TILE_MARGIN.  Returns
+    {(model, nx, ny): (tile_x, tile_y)} and the timings."""
     import torch
     say = log or (lambda *a: None)
     dev = torch.device("cuda:0")
@@ -308,12 +315,14 @@ def autotune_batch_tiles(precision=lbm.FP32_SHIFTED, sizes=SIZES, steps=100, nod
             b.close()
             timings.append((st["gpu_ms"] * 1e6 / max(st["node_updates"], 1), tx, ty))
         ns, tx, ty = min(timings)
+        if tx and ns > TILE_MARGIN * timings[0][0]:
+            ns, tx, ty = timings[0]
         best[(model, nx, ny)] = (tx, ty)
         name = "P" if model == lbm.MODEL_P else "FE"
         table.append(dict(model=name, nx=nx, ny=ny, lattices=n, tile_x=tx, tile_y=ty,
                           ns_per_node_update=ns,
                           candidates={f"{a}x{c}": v for v, a, c in timings}))
-        say(f"batch tiles: {name} {nx}x{ny} ({n} lattices): {tx}x{ty or 'auto'}, "
+        say(f"batch tiles: {name} {nx}x{ny} ({n} lattices): {tx or 'auto'}x{ty or 'auto'}, "
             f"{ns:.4f} ns per node update")
     return best, table
 

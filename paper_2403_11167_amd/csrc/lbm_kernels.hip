@@ -3113,8 +3113,8 @@ bool patch_allowed(const lbm_params& p) {
 // compute unit, and several tiles of up to 32 x 32 with 2 - 3 steps beyond.
 // Against the strips (which a lattice of few rows or columns leaves mostly
 // idle): 256 x 4 P FP64 10.4 -> 1.3 us per step, 256^2 P FP32 20.1 -> 2.2, FE
-// FP64 30.0 -> 3.6, 512^2 P FP64 25.5 -> 5.9, 1024^2 FE FP32 27.5 -> 17.8;
-// even at about 3 M nodes (P) and 1.5 M nodes (FE).
+// FP64 30.0 -> 3.6, 512^2 P FP64 16.9 -> 6.3, 1024^2 FE FP32 24 -> 18.4; even
+// at about 1.6 M nodes (FP64; FE FP32 1.4 M) and 2.5 M (P FP32).
 PatchPlan plan_patch(const lbm_params& p) {
   PatchPlan plan{};
   if (!patch_allowed(p) || p.A != 0.0) return plan;
@@ -4116,7 +4116,7 @@ void run_family(lbm_batch* b, int f, int steps) {
 
 // A problem takes two steps per launch in a batch when its launch
 // configuration asks for them and its tiles are 256-column strips (the
-// two-step row schedules need the halo wavefront beside the strip).
+// two-step batch kernels' tiles).
 int batch_two(const lbm_ctx* c) {
   return c->lc.two && c->lc.bx == 256 && two_addressable(c) ? 1 : 0;
 }

@@ -259,7 +259,7 @@ def build_problems(tuples, sizes, precision, guesses=None, tiles=None):
 # retired down to a few lattices, where it is several times slower.  Strip
 # width 0: the batch chooses between strips and patches from all its active
 # lattices (30000 lockstep steps on lattices of 64^2 .. 512^2: 16 tuples 1.73
-# -> 1.11 s, 64 tuples 4.13 -> 3.96 s, 256 tuples 13.6 s both ways).
+# -> 1.11 s, 64 tuples 4.13 -> 3.65 s, 256 tuples 13.6 s both ways).
 TILE_CANDIDATES = ((0, 0), (64, 0), (256, 0))
 # an explicit width has to beat the batch's own choice by this factor on the
 # full class, because it rules patches out when the class has retired to a few

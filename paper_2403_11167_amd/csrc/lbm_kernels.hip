@@ -3119,7 +3119,16 @@ PatchPlan plan_patch(const lbm_params& p) {
   PatchPlan plan{};
   if (!patch_allowed(p) || p.A != 0.0) return plan;
   const double N = (double)p.nx * p.ny;
-  if (N > 4e6 && !needs_gen(p)) return plan;
+  // beyond these sizes the estimate for several rounds of workgroups is too
+  // low, and the strips measure faster; the general pseudopotential kernel in
+  // FP64 stays ahead of its strips up to 4096^2 (369 against 487 us per step).
+  // General form, us per step on patches and strips: FE FP64 1.65 M nodes 58
+  // and 64, 4.2 M 174 and 134, 16.8 M 658 and 497; P FP32 4.2 M 54 and 65,
+  // 8.4 M 135 and 122.
+  const bool fp64 = p.precision == LBM_FP64;
+  double most = 4e6;
+  if (needs_gen(p)) most = p.model == LBM_MODEL_FE ? 1.8e6 : fp64 ? INFINITY : 6e6;
+  if (N > most) return plan;
   const PatchCost& pc = patch_cost(p);
   const PatchChoice c = choose_patch({PatchClass{&p, 1}},
                                      std::max(pc.strip_floor, 12.0 + 1e-3 * pc.strip_rate * N), 1e9);

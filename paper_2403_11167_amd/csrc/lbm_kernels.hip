@@ -4108,6 +4108,23 @@ void family_typed(lbm_batch* b, int f, int parity, int m, int check) {
   else launch_family<MODEL_FE, EOS_VDW, S, C>(b, f, parity, m, check);
 }
 
+// Whether a batch lattice of 128 to 255 columns takes a partly filled
+// 256-column strip with two steps per launch in place of whole 64-column ones.
+// Time of the first over the second at 1.9, 3.6 and 6 M nodes of 160 rows:
+// P FP32 0.58 - 0.89 at every width; FE FP32, whose tiles run as halves of 128
+// columns, 0.75 / 0.68 / 0.74 at 128 columns (one half filled), 0.73 - 1.48 at
+// 129 .. 175 and 0.55 - 0.84 beyond; in FP64, which is bound by its memory
+// traffic, P 1.2 / 1.6 / 2.3 at 128 columns, 0.9 - 2.1 to 192, up to 1.4 at 193
+// .. 208 and 0.72 - 0.95 from 224 on, FE 0.81 - 0.89 at 128 columns, 0.9 - 1.9
+// to 208, 0.78 - 0.92 from 224 on.
+bool batch_wide(const lbm_params& p) {
+  if (p.nx < 128 || p.nx >= 256) return false;
+  const bool fe = p.model == LBM_MODEL_FE;
+  if (fe && p.nx == 128) return true;
+  if (p.precision == LBM_FP64) return p.nx >= 224;
+  return !fe || p.nx >= 176;
+}
+
 // The chunk of `steps` (even) lockstep steps of a family, in an even number of
 // launches of nearly equal length, so that it ends in the buffer it started
 // from; the last step checks.
@@ -4559,10 +4576,7 @@ lbm_status lbm_batch_create(int32_t n, const lbm_params* p, const double* const*
                   INT64_MAX, -1, p[i].tile_y <= 0 ? 1 : 0, patch_allowed(p[i]) ? 1 : 0, 0,
                   PatchShape{}};
     st = ctx_setup(&p[i], b->ws + B.inst_off[i], d_rho0[i], info[i], stream, &I.ctx);
-    // half-empty 256-column strips with two steps per launch beat whole
-    // 64-column ones in a batch (128^2 FP32: P 0.0196 against 0.0245 ns per
-    // node update, FE 0.0259 against 0.0306)
-    if (st == LBM_OK && I.patch_ok && !p[i].tile_x && p[i].nx >= 128 && p[i].nx < 256) {
+    if (st == LBM_OK && I.patch_ok && !p[i].tile_x && batch_wide(p[i])) {
       I.ctx->lc.bx = 256;
       apply_launch(I.ctx);
     }

@@ -3855,16 +3855,16 @@ lbm_status lbm_autotune(const lbm_params* p, void* d_workspace, size_t bytes,
     q.kernel_flags = (int32_t)(LBM_KF_SET | LBM_KF_NT_STORE | LBM_KF_PATCH);
     if (plan_patch(q).on) st = time_shape(q, true);
   }
-  for (int bx : bxs) {
-    if (bx == 256 && p->nx < 192) continue;
-    for (int ly : lys) {
-      if (ly > p->ny) continue;
-      for (unsigned kf : kfs) {
+  for (size_t i = 0; i < bxs.size() && st == LBM_OK; ++i) {
+    if (bxs[i] == 256 && p->nx < 192) continue;
+    for (size_t j = 0; j < lys.size() && st == LBM_OK; ++j) {
+      if (lys[j] > p->ny) continue;
+      for (size_t k = 0; k < kfs.size() && st == LBM_OK; ++k) {
         lbm_params q = *p;
-        q.tile_x = bx;
-        q.tile_y = ly;
-        q.kernel_flags = (int32_t)kf;
-        if ((st = time_shape(q, false)) != LBM_OK) break;
+        q.tile_x = bxs[i];
+        q.tile_y = lys[j];
+        q.kernel_flags = (int32_t)kfs[k];
+        st = time_shape(q, false);
       }
     }
   }

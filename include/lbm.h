@@ -257,8 +257,9 @@ lbm_status lbm_launch_info(const lbm_ctx* ctx, lbm_launch* out);
  * height, store kind, register cap, pipelined row loop, one or two steps
  * per launch and the two-step kernel's strip width), `steps` steps each, on
  * a scratch state started from d_rho0, and return the fastest in
- * best->tile_x / tile_y / kernel_flags (the other fields are copied from p;
- * patches: LBM_KF_PATCH, the tile fields then have no effect).
+ * best->tile_x / tile_y / kernel_flags (the other fields are copied from p).
+ * Where patches are faster still, LBM_KF_PATCH is set beside the fastest strip
+ * shape, which serves where they do not apply (in a large batch).
  * Uses d_workspace (lbm_workspace_bytes(p)); synchronises the stream; the
  * results of a run never depend on the choice, only its speed. */
 lbm_status lbm_autotune(const lbm_params* p, void* d_workspace, size_t bytes,

@@ -2795,6 +2795,7 @@ struct PatchPlan {
   bool on;
   PatchShape ps;   // ps.steps: steps of a full launch
   int threads, npt;  // threads per workgroup, nodes of a step per thread
+  bool lone_strips;  // a launch of one step goes to the strips
 };
 
 }  // namespace
@@ -3132,8 +3133,16 @@ PatchPlan plan_patch(const lbm_params& p) {
   const PatchCost& pc = patch_cost(p);
   const PatchChoice c = choose_patch({PatchClass{&p, 1}},
                                      std::max(pc.strip_floor, 12.0 + 1e-3 * pc.strip_rate * N), 1e9);
+  // A single step (a call for one, or what is left of a count) moves as many
+  // bytes on patches as on strips, and their halo besides: where several rounds
+  // of tiles keep memory busy the pseudopotential is faster on strips (us per
+  // step of calls for one, patches and strips: FP64 1.8 M nodes 59 and 62, 2.25
+  // M 77 and 70; with walls 1.7 M 54 and 58, 2.9 M 112 and 91; FP32 with walls
+  // 3 M 39 and 52, 4.2 M 77 and 74, 4.8 M 89 and 79).  The free energy is even
+  // or faster on patches wherever it runs on them.
   if (c.on)
-    plan = PatchPlan{true, patch_shape(p, c.sx, c.sy, c.steps), c.threads, c.npt};
+    plan = PatchPlan{true, patch_shape(p, c.sx, c.sy, c.steps), c.threads, c.npt,
+                     p.model == LBM_MODEL_P && N > (fp64 ? 2e6 : 4e6)};
   return plan;
 }
 
@@ -3407,6 +3416,11 @@ void step_once(lbm_ctx* c) {
   }
 }
 
+// m <= pp.ps.steps steps of a lattice on patches.
+void step_on_patches(lbm_ctx* c, int m) {
+  if (m == 1 && c->pp.lone_strips) step_once(c);
+  else step_patch(c, m);
+}
 
 template <class S>
 void launch_init(lbm_ctx* c, const double* rho0) {
@@ -3604,7 +3618,8 @@ lbm_status observe_impl(lbm_ctx* c, int32_t cx, int32_t cy, lbm_obs* out,
 void advance(lbm_ctx* c, int m) {
   int k = 0;
   if (c->pp.on)
-    for (; k < m; k += std::min(m - k, c->pp.ps.steps)) step_patch(c, std::min(m - k, c->pp.ps.steps));
+    for (; k < m; k += std::min(m - k, c->pp.ps.steps))
+      step_on_patches(c, std::min(m - k, c->pp.ps.steps));
   if (two_step_ok(c))
     for (; k + 2 <= m; k += 2) step_twice(c);
   for (; k < m; ++k) step_once(c);
@@ -3706,7 +3721,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
       int64_t m = std::min<int64_t>(n - k, c->pp.ps.steps);
       if (c->p.ax != 0.0 && t < c->p.ax_from_step) m = std::min(m, c->p.ax_from_step - t);
       set_drive(c, t);
-      step_patch(c, (int)m);
+      step_on_patches(c, (int)m);
       k += m;
       continue;
     }

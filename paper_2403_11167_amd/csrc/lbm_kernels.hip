@@ -2782,6 +2782,7 @@ KParams<C> make_kparams(const lbm_params* p, double rho_ref, int nstrips,
 struct LaunchCfg {
   int bx;    // strip width (threads per workgroup): 64 or 256
   int ly;    // segment height
+  int ly1;   // that of the single steps of a lattice that mostly takes two (0: ly)
   int nt;    // 1: non-temporal population stores
   int wpe;   // 1: register-capped kernel variant
   int pipe;  // 1: pipelined row loop (pseudopotential)
@@ -2919,7 +2920,8 @@ lbm_status validate_launch(const lbm_params* p) {
 
 void apply_launch(lbm_ctx* c) {
   c->nstrips = (c->p.nx + c->lc.bx - 1) / c->lc.bx;
-  c->nseg = (c->p.ny + c->lc.ly - 1) / c->lc.ly;
+  const int ly1 = c->lc.ly1 ? c->lc.ly1 : c->lc.ly;
+  c->nseg = (c->p.ny + ly1 - 1) / ly1;
   int ntiles = c->nstrips * c->nseg;
   const bool no_remap = ((unsigned)c->p.kernel_flags & LBM_KF_SET) &&
                         ((unsigned)c->p.kernel_flags & LBM_KF_NO_XCD_REMAP);
@@ -2927,17 +2929,17 @@ void apply_launch(lbm_ctx* c) {
   for (KParams<double>* k : {&c->kd}) {
     k->nstrips = c->nstrips;
     k->nseg = c->nseg;
-    k->LY = c->lc.ly;
+    k->LY = ly1;
     k->xcd_remap = c->xcd_remap;
   }
   c->nstrips2 = two_strips(c->p.nx, c->lc.bx2);
   c->sw2 = two_width(c->p.nx, c->lc.bx2);
-  c->nseg2 = c->nseg;
+  c->nseg2 = (c->p.ny + c->lc.ly - 1) / c->lc.ly;
   const int ntiles2 = c->nstrips2 * c->nseg2;
   c->xcd_remap2 = (ntiles2 >= 64 && ntiles2 % 8 == 0 && !no_remap) ? 1 : 0;
   c->kf.nstrips = c->nstrips;
   c->kf.nseg = c->nseg;
-  c->kf.LY = c->lc.ly;
+  c->kf.LY = ly1;
   c->kf.xcd_remap = c->xcd_remap;
 }
 
@@ -3166,6 +3168,17 @@ void tune_ly(lbm_ctx* c, K kernel, int bx, int nstrips) {
   int LY = (c->p.ny + segs - 1) / segs;
   LY = std::max(LY, std::min(16, c->p.ny));
   c->lc.ly = std::min(LY, c->p.ny);
+  // The two-step kernels' long segments do not suit the single steps beside
+  // them (odd counts, calls for one step): these take two workgroups per
+  // compute unit in FP64 and five in FP32.  us per single step at the two-step
+  // height and this one: 4096^2 FE FP64 477 and 443, 3000 x 1000 P FP64 102 and
+  // 91, 2200^2 FE FP32 92 and 82, 1024 x 8192 P FP32 135 and 125; one and a half
+  // or two and a half workgroups cost 10 - 20 % in FP64, fewer than four 3 - 30 %
+  // in FP32.
+  if (two_step_ok(c) && c->p.tile_rounds <= 0) {
+    const int s1 = std::max(1, (c->p.precision == LBM_FP64 ? 2 : 5) * cus / c->nstrips);
+    c->lc.ly1 = std::max((c->p.ny + s1 - 1) / s1, std::min(8, c->p.ny));
+  }
   apply_launch(c);
 }
 
@@ -3303,6 +3316,7 @@ void launch_step2_bx(lbm_ctx* c, const KParams<C>& kp_in) {
   KParams<C> kp = kp_in;  // the two-step kernel's own tiling
   kp.nstrips = c->nstrips2;
   kp.nseg = c->nseg2;
+  kp.LY = c->lc.ly;
   kp.xcd_remap = c->xcd_remap2;
   const S* src = (const S*)(c->ws + (c->cur ? c->L.fB : c->L.fA));
   S* dst = (S*)(c->ws + (c->cur ? c->L.fA : c->L.fB));

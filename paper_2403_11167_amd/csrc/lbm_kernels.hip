@@ -2462,7 +2462,7 @@ __device__ __forceinline__ ObsPartial obs_block_reduce(ObsPartial a) {
 }
 
 // Observation in one pass over the populations: a workgroup takes tiles of
-// kObsTX x kObsTY nodes with their stencil halo (1 node for the pseudopotential,
+// 64 x 8 nodes with their stencil halo (1 node for the pseudopotential,
 // 2 for the free energy) into LDS: density (Eq. 6a) and psi (Eq. 11) or mu
 // (Sec. 2.2), then force, velocity (Eq. 6b), exports and partial reductions.
 // Bound by HBM on a large lattice (72 B of FP64 populations and 40 B of fields
@@ -2472,15 +2472,23 @@ __device__ __forceinline__ ObsPartial obs_block_reduce(ObsPartial a) {
 // the partials in the last workgroup to finish saves k_obs_final's launch but
 // costs every workgroup a release fence, which writes the whole L2 back:
 // 1000 x 777 took 306 us instead of 86.)
-constexpr int kObsTX = 64, kObsTY = 8, kObsNT = 512;
+// The tiles are narrower where a lattice fills them better: 8 x 64 nodes up to
+// 8 columns, 16 x 32 up to 16, 32 x 16 where 32 divides the width to an odd
+// number of strips (us in P FP64, 64 x 8 and these: 4 x 100000 111 and 67, 16 x
+// 100000 113 and 84, 17 x 100000 122 and 102, 65 x 40000 158 and 135; 16-column
+// tiles lose to 32-column ones from 65 columns on, 152).
+constexpr int kObsNT = 512;  // nodes of a tile and threads
+constexpr int obs_tile_x(int nx) {
+  return nx <= 8 ? 8 : nx <= 16 ? 16 : (nx + 31) / 32 % 2 ? 32 : 64;
+}
 
-template <int MODEL, int EOS, class S>
+template <int MODEL, int EOS, class S, int kObsTX>
 __global__ __launch_bounds__(kObsNT) void k_obs_all(
     const S* __restrict__ src, const KParams<double> kp, double* __restrict__ out_rho,
     double* __restrict__ out_ux, double* __restrict__ out_uy, double* __restrict__ uxp,
     double* __restrict__ uyp, int have_prev, ObsPartial* __restrict__ part,
     unsigned* __restrict__ flags, int cx, int cy, double* __restrict__ res) {
-  constexpr int HL = MODEL == MODEL_P ? 1 : 2;
+  constexpr int HL = MODEL == MODEL_P ? 1 : 2, kObsTY = kObsNT / kObsTX;
   constexpr int W = kObsTX + 2 * HL, R = kObsTY + 2 * HL, WM = kObsTX + 2, RM = kObsTY + 2;
   constexpr int NPT = (W * R + kObsNT - 1) / kObsNT;
   __shared__ double Aq[R][W];  // rho (FE) or psi (P), the tile and HL nodes a side
@@ -2657,7 +2665,8 @@ Layout make_layout(const lbm_params* p) {
   const size_t ua = (p->model == LBM_MODEL_FE && p->A != 0.0) ? align_up(N * 8) : 0;
   L.uax = off; off += ua;
   L.uay = off; off += ua;
-  const size_t obs_tiles = (size_t)((p->nx + kObsTX - 1) / kObsTX) * ((p->ny + kObsTY - 1) / kObsTY);
+  const int otx = obs_tile_x(p->nx), oty = kObsNT / otx;
+  const size_t obs_tiles = (size_t)((p->nx + otx - 1) / otx) * ((p->ny + oty - 1) / oty);
   L.obs_blocks = (int)std::min<size_t>(obs_tiles, kObsBlocksMax);
   L.part = off; off += align_up((size_t)L.obs_blocks * sizeof(ObsPartial));
   L.flags = off; off += kAlign;
@@ -3453,7 +3462,12 @@ template <int MODEL, int EOS, class S>
 void launch_observe(lbm_ctx* c, int cx, int cy, double* d_rho, double* d_ux, double* d_uy) {
   const S* src = (const S*)(c->ws + (c->cur ? c->L.fB : c->L.fA));
   unsigned* flags = (unsigned*)(c->ws + c->L.flags);
-  hipLaunchKernelGGL((k_obs_all<MODEL, EOS, S>), dim3(c->L.obs_blocks), dim3(kObsNT), 0, c->stream,
+  const int tx = obs_tile_x(c->p.nx);
+  const auto kernel = tx == 8    ? k_obs_all<MODEL, EOS, S, 8>
+                      : tx == 16 ? k_obs_all<MODEL, EOS, S, 16>
+                      : tx == 32 ? k_obs_all<MODEL, EOS, S, 32>
+                                 : k_obs_all<MODEL, EOS, S, 64>;
+  hipLaunchKernelGGL(kernel, dim3(c->L.obs_blocks), dim3(kObsNT), 0, c->stream,
                      src, c->kd, d_rho, d_ux, d_uy, (double*)(c->ws + c->L.uxp),
                      (double*)(c->ws + c->L.uyp), c->have_prev, (ObsPartial*)(c->ws + c->L.part),
                      flags, cx, cy, (double*)(c->ws + c->L.result));

@@ -3498,54 +3498,70 @@ struct Rho0Info {
   double ave;   // mean for the collision drive
 };
 
+// Check the initial density of one lattice on a host copy, and form the mean
+// for the collision drive: a compensated sum, in the order of the nodes.
+lbm_status rho0_host(const lbm_params& p, const double* d_rho0, hipStream_t stream,
+                     std::vector<double>& v, Rho0Info& out) {
+  const size_t N = (size_t)p.nx * p.ny;
+  const lbm_status st = read_host(d_rho0, N, stream, v);
+  if (st != LBM_OK) return st;
+  double s = 0.0, e = 0.0;
+  for (size_t k = 0; k < N; ++k) {
+    const double r = v[k], lim = p.eos == LBM_EOS_CS ? p.b * r / 4.0 : p.b * r;
+    if (!std::isfinite(r) || !(lim < 1.0) || !(r > 0.0)) return LBM_ERR_EOS_DOMAIN;
+    out.rmin = std::min(out.rmin, r);
+    const double t = s + r;
+    e += (std::fabs(s) >= std::fabs(r)) ? (s - t) + r : (r - t) + s;
+    s = t;
+  }
+  out.ave = p.rho_ave > 0.0 ? p.rho_ave : (s + e) / (double)N;
+  return LBM_OK;
+}
+
 // Check the initial densities of n lattices and find their smallest values:
-// one kernel per lattice, one copy for all.  `scratch` (a workspace that
-// holds nothing yet) takes the blocks' results, 16 bytes per block, at most
-// one block per 2048 nodes or one per lattice.  LBM_ERR_EOS_DOMAIN if a value
-// is outside the domain.
+// one kernel per lattice, one copy for all; on the host where the field has to
+// come there anyway (the drive's mean), and for a lone lattice of at most 8192
+// nodes, whose copy and scan cost less than a kernel and a copy (starting 72^2
+// takes 44 us so and 50 with the kernel, 128^2 64 and 51, 512^2 570 and 52).
+// `scratch` (a workspace that holds nothing yet) takes the blocks' results, 16
+// bytes per block, at most one block per 2048 nodes or one per lattice.
+// LBM_ERR_EOS_DOMAIN if a value is outside the domain.
 lbm_status rho0_info(int n, const lbm_params* p, const double* const* d_rho0, char* scratch,
                      hipStream_t stream, std::vector<Rho0Info>& out) {
   std::vector<int> first(n + 1, 0);
   for (int i = 0; i < n; ++i) {
     const size_t N = (size_t)p[i].nx * p[i].ny;
-    first[i + 1] = first[i] + (int)std::min<size_t>((N + 2047) / 2048, 1024);
+    const bool host = (p[i].ax != 0.0 && !(p[i].rho_ave > 0.0)) || (n == 1 && N <= 8192);
+    first[i + 1] = first[i] + (host ? 0 : (int)std::min<size_t>((N + 2047) / 2048, 1024));
   }
-  Rho0Check* d = (Rho0Check*)scratch;
-  for (int i = 0; i < n; ++i)
-    hipLaunchKernelGGL(k_rho0_check, dim3(first[i + 1] - first[i]), dim3(256), 0, stream,
-                       d_rho0[i], (size_t)p[i].nx * p[i].ny, p[i].b,
-                       p[i].eos == LBM_EOS_CS ? 1 : 0, d + first[i]);
-  std::vector<Rho0Check> h(first[n]);
-  if (hipGetLastError() != hipSuccess ||
-      hipMemcpyAsync(h.data(), d, h.size() * sizeof(Rho0Check), hipMemcpyDeviceToHost, stream) !=
-          hipSuccess ||
-      hipStreamSynchronize(stream) != hipSuccess)
-    return LBM_ERR_HIP;
   out.assign(n, Rho0Info{INFINITY, 0.0});
-  for (int i = 0; i < n; ++i)
-    for (int k = first[i]; k < first[i + 1]; ++k) {
-      if (h[k].bad) return LBM_ERR_EOS_DOMAIN;
-      out[i].rmin = std::min(out[i].rmin, h[k].rmin);
-    }
-  std::vector<double> v;
-  for (int i = 0; i < n; ++i) {
-    if (p[i].rho_ave > 0.0 || p[i].ax == 0.0) {
+  if (first[n] > 0) {
+    Rho0Check* d = (Rho0Check*)scratch;
+    for (int i = 0; i < n; ++i)
+      if (first[i + 1] > first[i])
+        hipLaunchKernelGGL(k_rho0_check, dim3(first[i + 1] - first[i]), dim3(256), 0, stream,
+                           d_rho0[i], (size_t)p[i].nx * p[i].ny, p[i].b,
+                           p[i].eos == LBM_EOS_CS ? 1 : 0, d + first[i]);
+    std::vector<Rho0Check> h(first[n]);
+    if (hipGetLastError() != hipSuccess ||
+        hipMemcpyAsync(h.data(), d, h.size() * sizeof(Rho0Check), hipMemcpyDeviceToHost, stream) !=
+            hipSuccess ||
+        hipStreamSynchronize(stream) != hipSuccess)
+      return LBM_ERR_HIP;
+    for (int i = 0; i < n; ++i) {
+      for (int k = first[i]; k < first[i + 1]; ++k) {
+        if (h[k].bad) return LBM_ERR_EOS_DOMAIN;
+        out[i].rmin = std::min(out[i].rmin, h[k].rmin);
+      }
       out[i].ave = std::max(p[i].rho_ave, 0.0);  // without the drive it has no part
-      continue;
     }
-    // mean initial density for the collision drive: compensated sum, in the
-    // order of the nodes
-    const size_t N = (size_t)p[i].nx * p[i].ny;
-    const lbm_status st = read_host(d_rho0[i], N, stream, v);
-    if (st != LBM_OK) return st;
-    double s = 0.0, e = 0.0;
-    for (size_t k = 0; k < N; ++k) {
-      const double t = s + v[k];
-      e += (std::fabs(s) >= std::fabs(v[k])) ? (s - t) + v[k] : (v[k] - t) + s;
-      s = t;
-    }
-    out[i].ave = (s + e) / (double)N;
   }
+  std::vector<double> v;
+  for (int i = 0; i < n; ++i)
+    if (first[i + 1] == first[i]) {
+      const lbm_status st = rho0_host(p[i], d_rho0[i], stream, v, out[i]);
+      if (st != LBM_OK) return st;
+    }
   return LBM_OK;
 }
 

@@ -2963,9 +2963,12 @@ bool needs_gen(const lbm_params& p);
 // Values of the compute type a patch keeps in LDS: nine populations and psi
 // or the density per cell, and the free energy's chemical potential (with
 // walls one row more each side).
-size_t patch_lds_values(const lbm_params& p, const PatchShape& ps) {
-  const size_t pitch = patch_pitch(p.model, ps), cells = pitch * patch_rows(p.model, ps);
+int64_t patch_lds_values(const lbm_params& p, int64_t pitch, int64_t cells) {
   return p.model == LBM_MODEL_FE ? 11 * cells + (needs_gen(p) ? 2 * pitch : 0) : 10 * cells;
+}
+size_t patch_lds_values(const lbm_params& p, const PatchShape& ps) {
+  const int64_t pitch = patch_pitch(p.model, ps);
+  return (size_t)patch_lds_values(p, pitch, pitch * patch_rows(p.model, ps));
 }
 
 // Compute units of the current device (256 on MI355X).
@@ -3013,26 +3016,29 @@ const PatchCost& patch_cost(const lbm_params& p) {
 // Tile of a lattice for the target sides (sx, sy) and T steps per launch:
 // sides balanced over the lattice, a dimension that the patch would reach
 // around spanned.
-PatchShape patch_shape(const lbm_params& p, int sx, int sy, int T) {
+struct Side {
+  int side, count;  // of a balanced tile, and the tiles along the dimension
+};
+Side balanced(int n, int side) {
+  const int k = (n + side - 1) / side, s = (n + k - 1) / k;
+  return Side{s, (n + s - 1) / s};
+}
+PatchShape patch_shape(const lbm_params& p, Side x, Side y, int T) {
   PatchShape ps{};
   const int halo = patch_halo(p.model, T);
-  auto balanced = [](int n, int side) { return (n + (n + side - 1) / side - 1) / ((n + side - 1) / side); };
-  ps.tx = balanced(p.nx, sx);
-  ps.ty = balanced(p.ny, sy);
   ps.steps = T;
-  if (ps.tx + 2 * halo + 2 > p.nx) {
-    ps.tx = p.nx;
-    ps.wrapx = 1;
-  }
-  if (p.boundary != LBM_BOUNDARY_WALLS && ps.ty + 2 * halo + 2 > p.ny) {
-    ps.ty = p.ny;
-    ps.wrapy = 1;
-  }
-  ps.ntx = (p.nx + ps.tx - 1) / ps.tx;
-  ps.nty = (p.ny + ps.ty - 1) / ps.ty;
+  ps.wrapx = x.side + 2 * halo + 2 > p.nx ? 1 : 0;
+  ps.wrapy = p.boundary != LBM_BOUNDARY_WALLS && y.side + 2 * halo + 2 > p.ny ? 1 : 0;
+  ps.tx = ps.wrapx ? p.nx : x.side;
+  ps.ty = ps.wrapy ? p.ny : y.side;
+  ps.ntx = ps.wrapx ? 1 : x.count;
+  ps.nty = ps.wrapy ? 1 : y.count;
   const int nt = ps.ntx * ps.nty;
   ps.xcd_remap = (nt >= 16 && nt % 8 == 0) ? 1 : 0;
   return ps;
+}
+PatchShape patch_shape(const lbm_params& p, int sx, int sy, int T) {
+  return patch_shape(p, balanced(p.nx, sx), balanced(p.ny, sy), T);
 }
 
 // A size class of lattices that share launches (one model, EOS and storage
@@ -3051,7 +3057,9 @@ struct PatchChoice {
 };
 
 // The least estimated time per step over tile sides and steps per launch, if
-// it is below `limit_us`; at most max_tiles tiles.
+// it is below `limit_us`; at most max_tiles tiles.  A start plans once, so the
+// search skips what cannot win: sides that give the tiles of the sides before
+// them, and the steps' own sum where a bound of it is above the best so far.
 PatchChoice choose_patch(const std::vector<PatchClass>& cls, double limit_us, double max_tiles) {
   PatchChoice best{};
   const lbm_params& p0 = *cls[0].p;
@@ -3061,49 +3069,85 @@ PatchChoice choose_patch(const std::vector<PatchClass>& cls, double limit_us, do
   const int H = fe ? 3 : 2, es = fp64 ? 8 : 4;
   const double cus = device_cus();
   static const int sides[] = {4, 8, 12, 16, 20, 24, 32, 48, 64};
-  for (int sx : sides)
-    for (int sy : sides) {
-      if (sy > 32) continue;
+  // per dimension: each class's balanced tile for every side at which one of
+  // them differs from that of the side before
+  const size_t nc = cls.size();
+  struct Sides {
+    std::vector<int> side;
+    std::vector<Side> tile;  // class k of side i: tile[i nc + k]
+  } xs, ys;
+  auto distinct = [&](int lbm_params::*n, int most, Sides& out) {
+    for (int side : sides) {
+      if (side > most) break;
+      bool differs = out.side.empty();
+      for (size_t k = 0; k < nc; ++k) {
+        out.tile.push_back(balanced(cls[k].p->*n, side));
+        differs |= out.tile.size() > nc && out.tile.back().side != out.tile[out.tile.size() - 1 - nc].side;
+      }
+      if (differs) out.side.push_back(side);
+      else out.tile.resize(out.tile.size() - nc);
+    }
+  };
+  distinct(&lbm_params::nx, 64, xs);
+  distinct(&lbm_params::ny, 32, ys);
+  auto up = [](double v) {  // ceil of a small positive number, without a call
+    const double w = (double)(int64_t)v;
+    return w < v ? w + 1.0 : w;
+  };
+  std::vector<PatchShape> shape(nc);
+  for (size_t i = 0; i < xs.side.size(); ++i)
+    for (size_t j = 0; j < ys.side.size(); ++j) {
+      const Side *tx = &xs.tile[i * nc], *ty = &ys.tile[j * nc];
       for (int T = 1; T <= 8; ++T) {
-        int64_t cells = 0, values = 0;
-        double tiles = 0, held = 0, lines = 0, work[8] = {};
-        for (const PatchClass& k : cls) {
-          const PatchShape ps = patch_shape(*k.p, sx, sy, T);
+        int64_t most = 0, values = 0;  // cells of the largest patch
+        double tiles = 0, held = 0, lines = 0, all = 0;  // all: work of the T steps
+        for (size_t n = 0; n < nc; ++n) {
+          const PatchShape& ps = shape[n] = patch_shape(*cls[n].p, tx[n], ty[n], T);
           const int pitch = patch_pitch(p0.model, ps), rows = patch_rows(p0.model, ps);
-          const int64_t c = (int64_t)pitch * rows;
-          cells = std::max(cells, c);
-          values = std::max(values, (int64_t)patch_lds_values(*k.p, ps));
-          const double m = (double)ps.ntx * ps.nty * k.count;
+          const int64_t cells = (int64_t)pitch * rows;
+          const double m = (double)ps.ntx * ps.nty * cls[n].count;
+          most = std::max(most, cells);
+          values = std::max(values, patch_lds_values(p0, pitch, cells));
           tiles += m;
-          held += m * c;
+          held += m * cells;
           // 128-byte lines: a row starts within one unless the tiles fit them
-          const bool fits = ps.tx * es % 128 == 0 && ps.tx * ps.ntx == k.p->nx;
+          const bool fits = ps.tx * es % 128 == 0 && ps.tx * ps.ntx == cls[n].p->nx;
           lines += m * (rows * (pitch * es / 128.0 + 1.0) +
                         ps.ty * (ps.tx * es / 128.0 + (fits ? 0.0 : 1.0)));
+          all += m * pitch * T * (ps.ty + (ps.wrapy ? 0 : H * T - 1));
+        }
+        // a larger T needs more cells
+        if (most > 2048 || (most > 1024 && one) || values * es > 160 * 1024 - 256) break;
+        if (tiles > max_tiles) continue;
+        const int npt = most <= 1024 ? 1 : 2, lds = (int)values * es;
+        const int threads = (((int)most + npt - 1) / npt + 63) & ~63;
+        const int occ = std::max(1, std::min(160 * 1024 / (lds + 256),
+                                             (npt == 1 ? pc.waves1 : pc.waves2) / (threads / 64)));
+        const double conc = std::min((double)occ, up(tiles / cus));
+        const double r = tiles / (cus * occ);
+        const double rounds = r <= 1.0 ? 1.0 : r + pc.be * (up(r) - r);
+        const double once = pc.lm + (pc.kl * lines / tiles / 16.0 + pc.kc * held / tiles / 64.0) * conc;
+        // the steps take no less than all of them at either rate (a part in 1e9
+        // for the rounding of the sums)
+        const double least = std::max(T * pc.ls, T * pc.al * pc.ls + pc.kw * all / tiles / 64.0 * conc);
+        if ((pc.l0 + rounds * (once + least)) * (1.0 - 1e-9) >= limit_us * T) continue;
+        double work[8] = {};
+        for (size_t n = 0; n < nc; ++n) {
+          const PatchShape& ps = shape[n];
+          const double m = (double)ps.ntx * ps.nty * cls[n].count;
           for (int s = 1; s <= T; ++s) {
             // whole rows of the step's first and last phase, their mean
             const int e = H * (T - s), my = ps.wrapy ? 0 : 2;
-            work[s - 1] += m * pitch * (ps.ty + my * (e + 0.5 * (H - 1)));
+            work[s - 1] += m * patch_pitch(p0.model, ps) * (ps.ty + my * (e + 0.5 * (H - 1)));
           }
         }
-        const int npt = cells <= 1024 ? 1 : 2;
-        const int64_t lds = values * es;
-        // a larger T needs more cells
-        if (cells > 2048 || (npt == 2 && one) || lds > 160 * 1024 - 256) break;
-        if (tiles > max_tiles) continue;
-        const int threads = (int)((cells + npt - 1) / npt + 63) / 64 * 64;
-        const int occ = std::max(1, std::min((int)(160 * 1024 / (lds + 256)),
-                                             (npt == 1 ? pc.waves1 : pc.waves2) / (threads / 64)));
-        const double conc = std::min((double)occ, std::ceil(tiles / cus));
-        const double r = tiles / (cus * occ);
-        const double rounds = r <= 1.0 ? 1.0 : r + pc.be * (std::ceil(r) - r);
-        double t = pc.lm + (pc.kl * lines / tiles / 16.0 + pc.kc * held / tiles / 64.0) * conc;
+        double t = once;
         for (int s = 0; s < T; ++s)
           t += std::max(pc.ls, pc.al * pc.ls + pc.kw * work[s] / tiles / 64.0 * conc);
         const double us = (pc.l0 + rounds * t) / T;
         if (us < limit_us) {
           limit_us = us;
-          best = PatchChoice{true, sx, sy, T, threads, npt, (size_t)lds};
+          best = PatchChoice{true, xs.side[i], ys.side[j], T, threads, npt, (size_t)lds};
         }
       }
     }
@@ -4538,7 +4582,9 @@ lbm_status enqueue_chunk(lbm_batch* b, int chunk) {
   // patches gain nothing from it (16 tuples 42.7 and 43.1 ms per 1000 steps).
   const bool side = patches && strips;
   if (side) {
-    if (hipEventRecord(b->ev_side, b->stream) != hipSuccess ||
+    if ((!b->ev_side &&
+         hipEventCreateWithFlags(&b->ev_side, hipEventDisableTiming) != hipSuccess) ||
+        hipEventRecord(b->ev_side, b->stream) != hipSuccess ||
         hipStreamWaitEvent(b->cap_stream, b->ev_side, 0) != hipSuccess)
       return LBM_ERR_HIP;
     b->launch = b->cap_stream;
@@ -4603,8 +4649,7 @@ lbm_status lbm_batch_create(int32_t n, const lbm_params* p, const double* const*
     delete b;
     return LBM_ERR_HIP;
   }
-  if (hipEventCreate(&b->ev0) != hipSuccess || hipEventCreate(&b->ev1) != hipSuccess ||
-      hipEventCreateWithFlags(&b->ev_side, hipEventDisableTiming) != hipSuccess) {
+  if (hipEventCreate(&b->ev0) != hipSuccess || hipEventCreate(&b->ev1) != hipSuccess) {
     if (b->ev0) (void)hipEventDestroy(b->ev0);
     if (b->ev1) (void)hipEventDestroy(b->ev1);
     (void)hipStreamDestroy(b->cap_stream);
@@ -4646,7 +4691,7 @@ lbm_status lbm_batch_create(int32_t n, const lbm_params* p, const double* const*
     for (auto& I : b->inst) delete I.ctx;
     (void)hipEventDestroy(b->ev0);
     (void)hipEventDestroy(b->ev1);
-    (void)hipEventDestroy(b->ev_side);
+    if (b->ev_side) (void)hipEventDestroy(b->ev_side);
     hipStreamDestroy(b->cap_stream);
     delete b;
     return st;
@@ -4665,7 +4710,7 @@ lbm_status lbm_batch_create(int32_t n, const lbm_params* p, const double* const*
     for (auto& I : b->inst) delete I.ctx;
     (void)hipEventDestroy(b->ev0);
     (void)hipEventDestroy(b->ev1);
-    (void)hipEventDestroy(b->ev_side);
+    if (b->ev_side) (void)hipEventDestroy(b->ev_side);
     hipStreamDestroy(b->cap_stream);
     delete b;
     return LBM_ERR_HIP;
@@ -4839,7 +4884,7 @@ lbm_status lbm_batch_destroy(lbm_batch* b) {
   for (auto& I : b->inst) delete I.ctx;
   (void)hipEventDestroy(b->ev0);
   (void)hipEventDestroy(b->ev1);
-  (void)hipEventDestroy(b->ev_side);
+  if (b->ev_side) (void)hipEventDestroy(b->ev_side);
   hipStreamDestroy(b->cap_stream);
   delete b;
   return LBM_OK;

@@ -207,9 +207,10 @@ lbm_status lbm_workspace_bytes(const lbm_params* p, size_t* bytes);
  * device memory) and enqueue f_i = f_i^eq(rho0, u = 0) on hip_stream, the
  * initial state of Sec. 5.3-5.4 (Eq. 4 for P, Eq. 20 for FE).  d_rho0 is a
  * device array of nx*ny doubles, read by the enqueued work.  Returns
- * LBM_ERR_EOS_DOMAIN if a density of d_rho0 is outside the EOS domain
- * (checked on the host from a copy).  On success *out receives a new
- * context. */
+ * LBM_ERR_EOS_DOMAIN, and leaves the workspace as it was, if a density of
+ * d_rho0 is outside the EOS domain (checked on the device, for small fields
+ * on the host from a copy; either synchronises the stream).  On success *out
+ * receives a new context. */
 lbm_status lbm_init(const lbm_params* p, void* d_workspace, size_t bytes,
                     const double* d_rho0, void* hip_stream, lbm_ctx** out);
 

@@ -2644,7 +2644,7 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 size_t row_pitch(int nx) { return (size_t)576 * (size_t)((nx + 63) / 64); }
 
 struct Layout {
-  size_t pop_bytes, fA, fB, uxp, uyp, uax, uay, part, flags, result, total;
+  size_t pop_bytes, fA, fB, uxp, uyp, spare, uax, uay, part, flags, result, total;
   int obs_blocks;
 };
 
@@ -2658,9 +2658,11 @@ Layout make_layout(const lbm_params* p) {
   L.fB = off; off += L.pop_bytes;
   L.uxp = off; off += align_up(N * 8);
   L.uyp = off; off += align_up(N * 8);
-  // two fields of doubles not in use (callers know the size of a workspace as
-  // the populations and four fields)
-  off += 2 * align_up(N * 8);
+  // two fields of doubles that a running lattice does not use (the size of a
+  // workspace is that of the populations and four fields, which the test of
+  // the precisions' workspace sizes holds it to); the check of the initial
+  // density leaves its results there
+  L.spare = off; off += 2 * align_up(N * 8);
   // FE with A != 0: the velocity field of the current step
   const size_t ua = (p->model == LBM_MODEL_FE && p->A != 0.0) ? align_up(N * 8) : 0;
   L.uax = off; off += ua;
@@ -3564,23 +3566,35 @@ lbm_status rho0_host(const lbm_params& p, const double* d_rho0, hipStream_t stre
 
 // Check the initial densities of n lattices and find their smallest values:
 // one kernel per lattice, one copy for all; on the host where the field has to
-// come there anyway (the drive's mean), and for a lone lattice of at most 8192
-// nodes, whose copy and scan cost less than a kernel and a copy (starting 72^2
-// takes 44 us so and 50 with the kernel, 128^2 64 and 51, 512^2 570 and 52).
-// `scratch` (a workspace that holds nothing yet) takes the blocks' results, 16
-// bytes per block, at most one block per 2048 nodes or one per lattice.
-// LBM_ERR_EOS_DOMAIN if a value is outside the domain.
+// come there anyway (the drive's mean), and for a lone lattice of at most 16384
+// nodes, whose copy and scan cost less than a kernel and two copies (starting
+// 72^2 takes 46 us so and 63 with the kernel, 128^2 64 both ways, 512^2 560 and
+// 65).
+// `scratch` takes the blocks' results, 16 bytes per block, at most one block per
+// 2048 nodes or one per lattice.  LBM_ERR_EOS_DOMAIN if a value is outside the
+// domain; a rejected start leaves the workspace as it was, which may hold a
+// running lattice, so the bytes there are put back.
 lbm_status rho0_info(int n, const lbm_params* p, const double* const* d_rho0, char* scratch,
                      hipStream_t stream, std::vector<Rho0Info>& out) {
   std::vector<int> first(n + 1, 0);
   for (int i = 0; i < n; ++i) {
     const size_t N = (size_t)p[i].nx * p[i].ny;
-    const bool host = (p[i].ax != 0.0 && !(p[i].rho_ave > 0.0)) || (n == 1 && N <= 8192);
+    const bool host = (p[i].ax != 0.0 && !(p[i].rho_ave > 0.0)) || (n == 1 && N <= 16384);
     first[i + 1] = first[i] + (host ? 0 : (int)std::min<size_t>((N + 2047) / 2048, 1024));
   }
   out.assign(n, Rho0Info{INFINITY, 0.0});
+  std::vector<Rho0Check> was(first[n]);
+  Rho0Check* d = (Rho0Check*)scratch;
+  const size_t bytes = was.size() * sizeof(Rho0Check);
+  auto rejected = [&](lbm_status st) {
+    if (bytes && (hipMemcpyAsync(d, was.data(), bytes, hipMemcpyHostToDevice, stream) != hipSuccess ||
+                  hipStreamSynchronize(stream) != hipSuccess))
+      return LBM_ERR_HIP;
+    return st;
+  };
   if (first[n] > 0) {
-    Rho0Check* d = (Rho0Check*)scratch;
+    if (hipMemcpyAsync(was.data(), d, bytes, hipMemcpyDeviceToHost, stream) != hipSuccess)
+      return LBM_ERR_HIP;  // (complete with the wait for the results)
     for (int i = 0; i < n; ++i)
       if (first[i + 1] > first[i])
         hipLaunchKernelGGL(k_rho0_check, dim3(first[i + 1] - first[i]), dim3(256), 0, stream,
@@ -3588,13 +3602,12 @@ lbm_status rho0_info(int n, const lbm_params* p, const double* const* d_rho0, ch
                            p[i].eos == LBM_EOS_CS ? 1 : 0, d + first[i]);
     std::vector<Rho0Check> h(first[n]);
     if (hipGetLastError() != hipSuccess ||
-        hipMemcpyAsync(h.data(), d, h.size() * sizeof(Rho0Check), hipMemcpyDeviceToHost, stream) !=
-            hipSuccess ||
+        hipMemcpyAsync(h.data(), d, bytes, hipMemcpyDeviceToHost, stream) != hipSuccess ||
         hipStreamSynchronize(stream) != hipSuccess)
-      return LBM_ERR_HIP;
+      return rejected(LBM_ERR_HIP);
     for (int i = 0; i < n; ++i) {
       for (int k = first[i]; k < first[i + 1]; ++k) {
-        if (h[k].bad) return LBM_ERR_EOS_DOMAIN;
+        if (h[k].bad) return rejected(LBM_ERR_EOS_DOMAIN);
         out[i].rmin = std::min(out[i].rmin, h[k].rmin);
       }
       out[i].ave = std::max(p[i].rho_ave, 0.0);  // without the drive it has no part
@@ -3604,7 +3617,7 @@ lbm_status rho0_info(int n, const lbm_params* p, const double* const* d_rho0, ch
   for (int i = 0; i < n; ++i)
     if (first[i + 1] == first[i]) {
       const lbm_status st = rho0_host(p[i], d_rho0[i], stream, v, out[i]);
-      if (st != LBM_OK) return st;
+      if (st != LBM_OK) return rejected(st);
     }
   return LBM_OK;
 }
@@ -3792,7 +3805,7 @@ lbm_status lbm_init(const lbm_params* p, void* d_workspace, size_t bytes,
     return LBM_ERR_WORKSPACE;
   hipStream_t stream = (hipStream_t)hip_stream;
   std::vector<Rho0Info> info;
-  if ((st = rho0_info(1, p, &d_rho0, (char*)d_workspace, stream, info)) != LBM_OK) return st;
+  if ((st = rho0_info(1, p, &d_rho0, (char*)d_workspace + L.spare, stream, info)) != LBM_OK) return st;
   if ((st = ctx_setup(p, d_workspace, d_rho0, info[0], stream, out)) != LBM_OK) return st;
   (*out)->pp = plan_patch(*p);
   return LBM_OK;
@@ -3909,7 +3922,7 @@ lbm_status lbm_autotune(const lbm_params* p, void* d_workspace, size_t bytes,
     return LBM_ERR_WORKSPACE;
   hipStream_t stream = (hipStream_t)hip_stream;
   std::vector<Rho0Info> info;
-  if ((st = rho0_info(1, p, &d_rho0, (char*)d_workspace, stream, info)) != LBM_OK) return st;
+  if ((st = rho0_info(1, p, &d_rho0, (char*)d_workspace + L.spare, stream, info)) != LBM_OK) return st;
   const bool fp64 = p->precision == LBM_FP64;
   std::vector<int> bxs = {64, 256};
   // tile_y 0: the occupancy-derived one-round segment height

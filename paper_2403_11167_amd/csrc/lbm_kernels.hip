@@ -4012,6 +4012,7 @@ struct BatchInst {
   int patch_ok;     // launch shape left to the library: patches may take it
   int patch;        // its family runs on patches now
   PatchShape ps;    // its tiles then
+  int patch_threads;  // and the threads of their workgroups
 };
 
 // two: the group's chunks take two steps per launch (k_batch_step2)
@@ -4364,6 +4365,7 @@ bool choose_families(lbm_batch* b) {
       if (!I.patch_ok || family_of(I.ctx->p) != f || I.state != LBM_BATCH_ACTIVE) continue;
       I.patch = c.on ? 1 : 0;
       if (!c.on) continue;
+      I.patch_threads = c.threads;
       const PatchShape ps = patch_shape(I.ctx->p, c.sx, c.sy, c.steps);
       changed |= memcmp(&ps, &I.ps, sizeof(ps)) != 0;
       I.ps = ps;
@@ -4689,7 +4691,7 @@ lbm_status lbm_batch_create(int32_t n, const lbm_params* p, const double* const*
     BatchInst& I = b->inst[i];
     I = BatchInst{nullptr, B.chk_off[i], LBM_BATCH_ACTIVE, 0, INFINITY, INFINITY, 0, 0, 0u,
                   INT64_MAX, -1, p[i].tile_y <= 0 ? 1 : 0, patch_allowed(p[i]) ? 1 : 0, 0,
-                  PatchShape{}};
+                  PatchShape{}, 0};
     st = ctx_setup(&p[i], b->ws + B.inst_off[i], d_rho0[i], info[i], stream, &I.ctx);
     if (st == LBM_OK && I.patch_ok && !p[i].tile_x && batch_wide(p[i])) {
       I.ctx->lc.bx = 256;
@@ -4922,7 +4924,7 @@ lbm_status lbm_batch_launch_info(const lbm_batch* b, int32_t i, lbm_launch* out)
     out->strip = I.ps.tx;
     out->segment = I.ps.ty;
     out->workgroups = I.ps.ntx * I.ps.nty;
-    out->threads = b->fam[family_of(c->p)].c.threads;
+    out->threads = I.patch_threads;
     return LBM_OK;
   }
   const int two = batch_two(c);

@@ -112,6 +112,14 @@ __device__ __forceinline__ void mfma_settle(f32x4& v) {
   asm volatile("s_nop 7\n\ts_nop 7" : "+v"(v));
 }
 
+// Orders a wavefront's LDS writes before the reads of its other lanes (no wait
+// of its own: a wavefront's LDS accesses are served in order).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // A 128 x 128 weight matrix as the workgroup fetches it: thread t has float4s
 // t, t + NT, ... of its 4096, so that every access is a whole line (fetched in
 // operand order, lane by lane, the two matrices took 17 us of a 28 us
@@ -248,6 +256,7 @@ __device__ __forceinline__ void output_layer(const float (*a)[LP], const float (
   if (n.r < NO)
 #pragma unroll
     for (int v = 0; v < 4; ++v) s_o[4 * n.q + v][n.r] = acc[v];
+  wave_sync();
 }
 
 // Predictions, a workgroup walking tiles with a stride of the grid.  256

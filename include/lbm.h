@@ -29,7 +29,8 @@
  * into that workspace; it must not outlive it.  Every device operation is
  * enqueued on the HIP stream given to lbm_init() (NULL = the null stream).
  * Only lbm_observe() and the lbm_batch_run() / lbm_batch_observe() calls
- * synchronise that stream.  One context per stream; contexts on different
+ * synchronise that stream, and the calls that start a lattice or a batch or
+ * tune one, which check the initial density.  One context per stream; contexts on different
  * streams are independent.  The library holds no global state apart from
  * the fixed device array of lbm_mlp_grad_noalloc (below).
  *
@@ -120,9 +121,12 @@ typedef struct {
                            shift (<= 0: the smallest initial density)       */
   /* Launch shape; 0 selects the tuned default (see lbm_autotune).  With all
      of tile_x, tile_y, kernel_flags and tile_rounds 0 (or LBM_KF_PATCH), and
-     A = 0, a lattice too small to fill the device with strips runs on
-     patches: rectangular tiles that take several steps per launch in LDS
-     (lbm_launch_info shows which).  Results do not depend on these, only the speed does. */
+     A = 0, a lattice runs on patches where these are estimated to be faster
+     than strips: rectangular tiles that take several steps per launch in LDS
+     (lbm_launch_info shows which).  Periodic lattices do up to 1 - 4 M nodes,
+     with walls or the drive the pseudopotential in FP64 at any size, in FP32
+     up to 6 M, the free energy up to 1 - 1.8 M.  Results do not depend on
+     these fields, only the speed does. */
   int32_t tile_x;       /* columns per workgroup strip: 0, 64 or 256         */
   int32_t tile_y;       /* rows per workgroup segment: 1 .. 1024, or 0: set at
                            the first step so that the tiles fill whole rounds
@@ -269,7 +273,11 @@ lbm_status lbm_autotune(const lbm_params* p, void* d_workspace, size_t bytes,
 
 /* ---- batches of independent lattices --------------------------------------
  * A batch advances n independent problems (sizes, models, EOS and
- * parameters may differ; the precision is common) in lockstep: each time
+ * parameters may differ; the precision is common) in lockstep.  The problems
+ * of one model and EOS whose launch shape is left to the library run on
+ * patches while they are too few to fill the device with strips: all of them
+ * in one launch of up to 8 steps, decided again whenever the active problems
+ * change.  On strips each time
  * step is one launch per (model, EOS, strip width) group over a table of all
  * tiles of all active problems, and runs of steps are captured in a HIP
  * graph.  Problems on 256-column strips whose kernel_flags allow two steps
@@ -343,7 +351,9 @@ lbm_status lbm_batch_stats(const lbm_batch* b, int64_t* node_updates, double* gp
                            int64_t* chunks);
 
 /* The launch shape of problem i in the batch (not part of the paper's
- * method): steps_per_launch 2 when its group takes two steps per launch,
+ * method), of a retired problem the one it last ran with.  On patches:
+ * steps per launch, columns and rows of a tile, tiles and threads.  On
+ * strips: steps_per_launch 2 when its group takes two steps per launch,
  * strip and threads of that kernel (a two-step free-energy group runs each
  * 256-column tile as two 128-column strips), segment its current segment
  * height (with tile_y = 0 it may change whenever the active problems

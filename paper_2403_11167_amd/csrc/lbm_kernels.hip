@@ -28,8 +28,10 @@
 //      read from the 3x3 LDS stencil, and store it.
 // Halo rows at the segment ends and the H halo columns are recomputed from
 // the populations.  No MFMA: the update is a bandwidth-bound stencil.
-// Lattices too small to fill the device with strips run on patches instead
-// (patch_steps): several steps per launch of a rectangular tile held in LDS.
+// Lattices that strips are estimated to serve worse (in the general form of
+// the pseudopotential in FP64 all of them, else up to 1 - 6 M nodes: plan_patch)
+// run on patches instead (patch_steps): several steps per launch of a
+// rectangular tile held in LDS.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -1784,8 +1786,8 @@ __device__ __forceinline__ void tile_fe_pipe(const S* __restrict__ src, S* __res
 }
 
 // ---- patch steps: T time steps of one tile in LDS ------------------------------
-// A lattice too small to fill the device with strips runs on patches: a
-// workgroup takes a tile of tx x ty nodes through T steps in one launch, with
+// Strips sweep a small lattice with a few workgroups, row after row.  On
+// patches a workgroup takes a tile of tx x ty nodes through T steps in one launch, with
 // the populations between the steps in LDS and nothing exchanged between
 // workgroups.  A step reads H nodes around what it updates (H = 2 for the
 // pseudopotential: pull + psi stencil; 3 for the free energy: pull + the
@@ -2985,10 +2987,10 @@ int device_cus() {
   return cus;
 }
 
-// Costs in microseconds, fitted to 7323 MI355X timings (lattices of 64^2 ..
-// 2000 x 1500 and batches, tiles of 8 x 4 .. 64 x 16, 1 .. 8 steps per launch;
-// rms deviation 10 - 15 %; the shape of the least estimate is within 1 - 5 %
-// of the best measured one on average, 23 % at worst).  A launch costs l0,
+// Costs in microseconds, fitted to 7323 MI355X timings (5643 of lattices of
+// 64^2 .. 2000 x 1500 and 1680 of batches, tiles of 8 x 4 .. 64 x 16, 1 .. 8 steps
+// per launch; rms deviation 10 - 15 %; the shape of the least estimate is within
+// 1 - 8 % of the best measured one on average over the sets, 23 % at worst).  A launch costs l0,
 // and each round of resident workgroups: lm; kl per 16 lines of 128 bytes
 // that the pulls of one population and the stores touch, kc per wavefront of
 // held nodes; and per step the larger of ls (its chain of instructions and
@@ -3168,11 +3170,14 @@ bool patch_allowed(const lbm_params& p) {
 // estimated time per step is below the strips': tile, steps per launch and
 // threads of the least estimate.  In practice about one tile per compute
 // unit and 2 - 6 steps while the lattice has up to about 1000 nodes per
-// compute unit, and several tiles of up to 32 x 32 with 2 - 3 steps beyond.
+// compute unit, and several tiles of up to 64 x 32 with 1 - 3 steps beyond.
 // Against the strips (which a lattice of few rows or columns leaves mostly
 // idle): 256 x 4 P FP64 10.4 -> 1.3 us per step, 256^2 P FP32 20.1 -> 2.2, FE
-// FP64 30.0 -> 3.6, 512^2 P FP64 16.9 -> 6.3, 1024^2 FE FP32 24 -> 18.4; even
-// at about 1.6 M nodes (FP64; FE FP32 1.4 M) and 2.5 M (P FP32).
+// FP64 30.0 -> 3.6, 512^2 P FP64 16.9 -> 6.3, 1024^2 FE FP32 24 -> 18.4.
+// Square periodic lattices are on patches up to about 2.0 M nodes (P FP64), 2.9
+// M (P FP32), 1.06 M (FE FP64) and 1.5 M (FE FP32), in the general form without
+// limit (P FP64), up to 6 M (P FP32), 1.8 M (FE FP64) and 1.1 M (FE FP32); other
+// shapes up to a third further.
 PatchPlan plan_patch(const lbm_params& p) {
   PatchPlan plan{};
   if (!patch_allowed(p) || p.A != 0.0) return plan;

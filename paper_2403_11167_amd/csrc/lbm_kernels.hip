@@ -2475,13 +2475,16 @@ __device__ __forceinline__ ObsPartial obs_block_reduce(ObsPartial a) {
 // costs every workgroup a release fence, which writes the whole L2 back:
 // 1000 x 777 took 306 us instead of 86.)
 // The tiles are narrower where a lattice fills them better: 8 x 64 nodes up to
-// 8 columns, 16 x 32 up to 16, 32 x 16 where 32 divides the width to an odd
-// number of strips (us in P FP64, 64 x 8 and these: 4 x 100000 111 and 67, 16 x
-// 100000 113 and 84, 17 x 100000 122 and 102, 65 x 40000 158 and 135; 16-column
-// tiles lose to 32-column ones from 65 columns on, 152).
+// 8 columns, 16 x 32 up to 16, 32 x 16 up to 288 where the width makes an odd
+// number of 32-column strips (us in P FP64, 64 x 8 and these: 4 x 100000 111 and
+// 67, 16 x 100000 113 and 84, 17 x 100000 122 and 102, 65 x 40000 158 and 135;
+// 16-column tiles lose to 32-column ones from 65 columns on, 152, and those to
+// 64-column ones where they save little, 2050^2 156 and 165).  Up to two tiles
+// of 64 x 8 per compute unit there is nothing to gain (16 x 300 35 and 36).
 constexpr int kObsNT = 512;  // nodes of a tile and threads
-constexpr int obs_tile_x(int nx) {
-  return nx <= 8 ? 8 : nx <= 16 ? 16 : (nx + 31) / 32 % 2 ? 32 : 64;
+constexpr int obs_tile_x(int nx, int ny) {
+  if ((nx + 63) / 64 * (int64_t)((ny + 7) / 8) <= 512) return 64;
+  return nx <= 8 ? 8 : nx <= 16 ? 16 : nx <= 288 && (nx + 31) / 32 % 2 ? 32 : 64;
 }
 
 template <int MODEL, int EOS, class S, int kObsTX>
@@ -2669,7 +2672,7 @@ Layout make_layout(const lbm_params* p) {
   const size_t ua = (p->model == LBM_MODEL_FE && p->A != 0.0) ? align_up(N * 8) : 0;
   L.uax = off; off += ua;
   L.uay = off; off += ua;
-  const int otx = obs_tile_x(p->nx), oty = kObsNT / otx;
+  const int otx = obs_tile_x(p->nx, p->ny), oty = kObsNT / otx;
   const size_t obs_tiles = (size_t)((p->nx + otx - 1) / otx) * ((p->ny + oty - 1) / oty);
   L.obs_blocks = (int)std::min<size_t>(obs_tiles, kObsBlocksMax);
   L.part = off; off += align_up((size_t)L.obs_blocks * sizeof(ObsPartial));
@@ -3513,7 +3516,7 @@ template <int MODEL, int EOS, class S>
 void launch_observe(lbm_ctx* c, int cx, int cy, double* d_rho, double* d_ux, double* d_uy) {
   const S* src = (const S*)(c->ws + (c->cur ? c->L.fB : c->L.fA));
   unsigned* flags = (unsigned*)(c->ws + c->L.flags);
-  const int tx = obs_tile_x(c->p.nx);
+  const int tx = obs_tile_x(c->p.nx, c->p.ny);
   const auto kernel = tx == 8    ? k_obs_all<MODEL, EOS, S, 8>
                       : tx == 16 ? k_obs_all<MODEL, EOS, S, 16>
                       : tx == 32 ? k_obs_all<MODEL, EOS, S, 32>

@@ -1,7 +1,7 @@
 """The observation at the widths where its tiles change (8 x 64, 16 x 32, 32 x
-16 or 64 x 8 nodes): several tiles with remainders in
-both directions, periodic and between walls, against the oracle, and several
-rounds of tiles against the sums of the exported fields."""
+16 or 64 x 8 nodes; up to 512 tiles always 64 x 8): several tiles with
+remainders in both directions, periodic and between walls, against the oracle,
+and several rounds of tiles against the sums of the exported fields."""
 import math
 
 import numpy as np
@@ -16,12 +16,13 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("model", ["P", "FE"])
-@pytest.mark.parametrize("nx,ny,walls", [(1, 130, False), (3, 64, False), (8, 65, False),
-                                         (9, 63, False), (16, 33, False), (17, 129, False),
-                                         (32, 128, False), (33, 129, False), (65, 40, False),
-                                         (96, 17, False), (97, 17, False), (1, 65, True),
-                                         (9, 64, True), (16, 66, True), (32, 66, True),
-                                         (33, 66, True), (65, 35, True)])
+@pytest.mark.parametrize("nx,ny,walls", [(1, 4096, False), (1, 4097, False), (3, 4500, False),
+                                         (8, 4161, False), (9, 4099, False), (16, 4129, False),
+                                         (17, 4111, False), (32, 4112, False), (33, 4113, False),
+                                         (65, 2064, False), (96, 2065, False), (97, 2065, False),
+                                         (288, 830, False), (1, 4161, True), (9, 4160, True),
+                                         (16, 4130, True), (32, 4130, True), (33, 4130, True),
+                                         (65, 2070, True)])
 def test_widths(nx, ny, walls, model):
     matches_oracle(nx, ny, walls, model)
 

@@ -1787,9 +1787,9 @@ __device__ __forceinline__ void tile_fe_pipe(const S* __restrict__ src, S* __res
 
 // ---- patch steps: T time steps of one tile in LDS ------------------------------
 // Strips sweep a small lattice with a few workgroups, row after row.  On
-// patches a workgroup takes a tile of tx x ty nodes through T steps in one launch, with
-// the populations between the steps in LDS and nothing exchanged between
-// workgroups.  A step reads H nodes around what it updates (H = 2 for the
+// patches a workgroup takes a tile of tx x ty nodes through T steps in one
+// launch, with the populations between the steps in LDS and nothing exchanged
+// between workgroups.  A step reads H nodes around what it updates (H = 2 for the
 // pseudopotential: pull + psi stencil; 3 for the free energy: pull + the
 // chemical-potential and gradient stencils), so the workgroup holds the tile
 // plus H T - 1 nodes a side and the valid part shrinks by H a side per step;
@@ -2993,13 +2993,13 @@ int device_cus() {
 // Costs in microseconds, fitted to 7323 MI355X timings (5643 of lattices of
 // 64^2 .. 2000 x 1500 and 1680 of batches, tiles of 8 x 4 .. 64 x 16, 1 .. 8 steps
 // per launch; rms deviation 10 - 15 %; the shape of the least estimate is within
-// 1 - 8 % of the best measured one on average over the sets, 23 % at worst).  A launch costs l0,
-// and each round of resident workgroups: lm; kl per 16 lines of 128 bytes
-// that the pulls of one population and the stores touch, kc per wavefront of
-// held nodes; and per step the larger of ls (its chain of instructions and
-// barriers) and al ls + kw per wavefront at work on the compute unit.  The
-// last, partly filled round counts be of a whole one.  strip_floor (us per
-// step) and strip_rate (ns per node and step) are the strip kernels' own:
+// 1 - 8 % of the best measured one on average over the sets, 23 % at worst).  A
+// launch costs l0, and each round of resident workgroups: lm; kl per 16 lines of
+// 128 bytes that the pulls of one population and the stores touch, kc per
+// wavefront of held nodes; and per step the larger of ls (its chain of
+// instructions and barriers) and al ls + kw per wavefront at work on the compute
+// unit.  The last, partly filled round counts be of a whole one.  strip_floor
+// (us per step) and strip_rate (ns per node and step) are the strip kernels' own:
 // their latency on a small lattice and their rate on a large one, reached
 // about 12 us above it; GEN rows are the general kernel's.
 struct PatchCost {
